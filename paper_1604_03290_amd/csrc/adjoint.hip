@@ -241,13 +241,6 @@ struct AdjOwn {
     bool tens;  // negative pressure (the record's sign bit)
 };
 
-// Murnaghan sound speed of a partner from its density, as the forward prepass forms it
-__device__ inline double murnaghan_c(const Consts &k, double rho) {
-    const double eta = rho / k.rho0;
-    const double en1 = pow(eta, k.n_M - 1.0);
-    return sqrt(k.K0 / k.rho0 * en1);
-}
-
 // Both roles of the pair (c, b) (see the file header).  b = forward record chunks
 // b0..b6 of the partner (its mass is V rho), e0..e6 = its adjoint record chunks.  With the
 // correction, Mc and Mb are the symmetrised cotangents of the moment matrices
@@ -261,7 +254,7 @@ __device__ inline void adj_pair(const Consts &k, const AdjOwn &o, double d2, dou
                                 double2 e4, double2 e5, double2 e6, AdjAcc &acc,
                                 const double *Mc = nullptr, const double *Mb = nullptr,
                                 const double *xo = nullptr, const double *xb = nullptr,
-                                double cb = 0.0 /* Tillotson: partner's signed c */) {
+                                double cb = 0.0 /* Murnaghan, Tillotson: the partner's signed c */) {
     const double Gn = k.Fn * k.inv_h * k.inv_h;
     const double Lbb[9] = {e0.x, e0.y, e1.x, e1.y, e2.x, e2.y, e3.x, e3.y, e4.x};
     const double rx = o.xc - b0.x, ry = o.yc - b0.y, rz = o.zc - b1.x;
@@ -284,8 +277,7 @@ __device__ inline void adj_pair(const Consts &k, const AdjOwn &o, double d2, dou
     for (int i = 0; i < 9; ++i) M[i] = Vb * o.Lbc[i] + o.Vc * Lbb[i];
     const double w = -(ux * rx + uy * ry + uz * rz);
     double alpha_c = k.alpha_c;
-    if constexpr (kEos == 1) alpha_c = k.alpha * (0.5 * (o.cc + murnaghan_c(k, rb_)));
-    if constexpr (kEos == 2) alpha_c = k.alpha * (0.5 * (o.cc + fabs(cb)));
+    if constexpr (kEos != 0) alpha_c = k.alpha * (0.5 * (o.cc + fabs(cb)));
     const Visc vs = viscosity(k, d2, w, o.rc, rb_, alpha_c);
     const double Pi = vs.Pi;
     double B0 = o.Tc[0] + b4.x - Pi, B1 = o.Tc[1] + b4.y - Pi;
@@ -527,7 +519,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_pairs(GridDev g, int64_t n, Cons
             }
             adj_pair<kCorr, kEos, kAS, kXC>(k, o, d2, b0, b1, rb[2], rb[3], rb[4], rb[5], rb[6],
                                             qb[0], qb[1], qb[2], qb[3], qb[4], qb[5], qb[6], acc,
-                                            Mc, Mb, xo, xb, kEos == 2 ? rb[7].y : 0.0);
+                                            Mc, Mb, xo, xb, kEos != 0 ? rb[7].y : 0.0);
         });
         if (kXC) {  // dx/dt = v + ...
             acc.gvx += xo[1];
@@ -542,8 +534,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_pairs(GridDev g, int64_t n, Cons
 
 // the same over the frozen pair list: a workgroup of kSplitAdj wavefronts takes one
 // block of 64 slots, wavefront q evaluating steps q, q + kSplitAdj, ... (the first seven
-// chunks of each partner's two records gathered cooperatively; with Tillotson all eight
-// of the forward record, whose last holds the partner's signed sound speed); the
+// chunks of each partner's two records gathered cooperatively; with Murnaghan and
+// Tillotson all eight of the forward record, whose last holds the partner's signed sound
+// speed); the
 // partial sums are folded into wavefront 0, which runs the pre stage and the Y0 sum.
 // With the du and dx/dt cotangents each lane loads its own partner's four (one list
 // entry per lane and step)
@@ -552,7 +545,7 @@ __global__ __launch_bounds__(64 * kSplitAdj) void k_adj_pairs_list(GridDev g, in
                                                                    const double *__restrict__ rec,
                                                                    StateDev st, AdjRec ad,
                                                                    GradDev out) {
-    constexpr int kF = kEos == 2 ? 8 : 7;  // forward-record chunks gathered
+    constexpr int kF = kEos != 0 ? 8 : 7;  // forward-record chunks gathered
     __shared__ double2 lbuf[kSplitAdj][64 * (kF + 7)];
     const int q = threadIdx.x >> 6;
     double2 *bf = lbuf[q];

@@ -19,21 +19,6 @@ namespace {
 
 constexpr int kWave = 64;
 
-__global__ __launch_bounds__(kBlock) void k_pl_gather(GridDev g, const double *__restrict__ x,
-                                                      const double *__restrict__ y,
-                                                      const double *__restrict__ z, int64_t n,
-                                                      double *__restrict__ x0,
-                                                      int32_t *__restrict__ status) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const int a = g.perm[s];
-    const double px = x[a], py = y[a], pz = z[a];
-    if (!within_cell(g, (int)s, px, py, pz)) raise_flag(status, SPH_ERR_STALE_GRID);
-    x0[3 * s + 0] = px;
-    x0[3 * s + 1] = py;
-    x0[3 * s + 2] = pz;
-}
-
 // Distance from the interval [b0, b1] to the slab of cell i along one axis (the
 // first and last cells extend to infinity, as in slab_gap).
 __device__ inline double box_gap(double b0, double b1, double lo, double cell, int i, int ncell) {
@@ -57,18 +42,31 @@ __device__ inline double wave_max(double v) {
     return v;
 }
 
-// Upper bound of every slot's candidates: the slots of the cells within reach of its
-// position (each candidate lies in one of them, within delta of its cell's box), self
-// included.
-__global__ __launch_bounds__(kBlock) void k_pl_bound(GridDev g, const double *__restrict__ x0,
-                                                     int64_t n, double reach,
-                                                     int32_t *__restrict__ bound) {
+// Gathers the positions into slot order and bounds every slot's candidates: the slots of
+// the cells within reach of its position (each candidate lies in one of them, within delta
+// of its cell's box), self included.  sizes[B] = 64 * (largest bound of block B).  (The
+// gather, the bounds and the blocks' largest in three passes took 35 us on 30,000
+// particles and 133 on a million; this takes 21 and 110.)
+__global__ __launch_bounds__(kBlock) void k_pl_bound(GridDev g, const double *__restrict__ x,
+                                                     const double *__restrict__ y,
+                                                     const double *__restrict__ z, int64_t n,
+                                                     double reach, double *__restrict__ x0,
+                                                     int64_t *__restrict__ sizes,
+                                                     int32_t *__restrict__ status) {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
     int b = 0;
-    for_each_row(g, x0[3 * s], x0[3 * s + 1], x0[3 * s + 2], reach,
-                 [&](int s0, int s1) { b += s1 - s0; });
-    bound[s] = b;
+    if (s < n) {
+        const int a = g.perm[s];
+        const double px = x[a], py = y[a], pz = z[a];
+        if (!within_cell(g, (int)s, px, py, pz)) raise_flag(status, SPH_ERR_STALE_GRID);
+        x0[3 * s + 0] = px;
+        x0[3 * s + 1] = py;
+        x0[3 * s + 2] = pz;
+        for_each_row(g, px, py, pz, reach, [&](int s0, int s1) { b += s1 - s0; });
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) b = max(b, __shfl_xor(b, o));
+    if (__lane_id() == 0 && s < n) sizes[s / kWave] = (int64_t)kWave * b;
 }
 
 // Fill pass, one wavefront per group of 64 slots.  The fill writes entry j of lane l
@@ -108,7 +106,8 @@ __global__ __launch_bounds__(kBlock) void k_pl_fill(GridDev g, const double *__r
     int32_t *run_pre = lds_r[threadIdx.x >> 6][1];  // candidates before it in the pass
     const int lane = __lane_id();
     const int64_t nb = (n + kWave - 1) / kWave;
-    const int64_t B = (int64_t)blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
+    // (neighbouring groups on one XCD: a million particles 715 us in launch order, 660 so)
+    const int64_t B = xcd_block(gridDim.x) * (kBlock / kWave) + (threadIdx.x >> 6);
     if (B >= nb) return;  // whole wavefront past the end
     const int64_t s = B * kWave + lane;
     const bool act = s < n;
@@ -322,17 +321,6 @@ __global__ __launch_bounds__(kBlock) void k_pl_fill(GridDev g, const double *__r
     }
 }
 
-// sizes[B] = 64 * (largest bound of block B)
-__global__ __launch_bounds__(kBlock) void k_pl_sizes(const int32_t *__restrict__ count, int64_t n,
-                                                     int64_t *__restrict__ sizes) {
-    const int64_t B = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nb = (n + kWave - 1) / kWave;
-    if (B >= nb) return;
-    int m = 0;
-    for (int64_t s = B * kWave; s < min((B + 1) * kWave, n); ++s) m = max(m, count[s]);
-    sizes[B] = (int64_t)kWave * m;
-}
-
 }  // namespace
 
 size_t pairs_ws_bytes(int64_t n) {
@@ -374,13 +362,8 @@ extern "C" int sph_build_pairs(sph_grid *grid, const double *x, const double *y,
     const double r2 = radius * radius * (1.0 + 1e-12);
     const double reach = (radius + g.delta) * (1.0 + 1e-9);
     if ((rc = clear_status(ws, s))) return rc;
-    k_pl_gather<<<blocks_for(n), kBlock, 0, s>>>(g, x, y, z, n, x0, c.status());
-    SPH_LAUNCHED();
     const double h2 = grid->h * grid->h;  // the partner test of sph_neighbours at grid->h
-    // bounds into count (the fill overwrites them with the counts)
-    k_pl_bound<<<blocks_for(n), kBlock, 0, s>>>(g, x0, n, reach, count);
-    SPH_LAUNCHED();
-    k_pl_sizes<<<blocks_for(nb), kBlock, 0, s>>>(count, n, sizes);
+    k_pl_bound<<<blocks_for(n), kBlock, 0, s>>>(g, x, y, z, n, reach, x0, sizes, c.status());
     SPH_LAUNCHED();
     if ((rc = exclusive_scan_i64(sizes, block_start, nb, tmp, s))) return rc;
     int64_t total = 0;

@@ -80,8 +80,10 @@ enum sph_op {
  * steps: the largest count among its slots) with the slot itself (n - 1 for the
  * lanes of the last group past n), so every entry of those steps is a valid slot.
  * The group's room, block_start[B + 1] - block_start[B], is 64 times the largest
- * upper bound of its slots' counts and may exceed 64 times its steps; entries past
- * the steps are not written.  All arrays are device arrays owned by the caller. */
+ * upper bound of its slots' counts and may exceed 64 times its steps; what lies past
+ * the steps is the library's own (with a skin, hints from which its kernels find the same
+ * entries' records faster; they count for nothing where they do not agree with the entries, and
+ * need not be copied with them).  All arrays are device arrays owned by the caller. */
 typedef struct {
     int64_t n;             /* slots */
     double radius;         /* h + skin at build time */

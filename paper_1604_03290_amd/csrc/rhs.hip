@@ -22,6 +22,7 @@
 #include "common.hpp"
 #include "rhs_common.hpp"
 #include "timing.hpp"
+#include "window.hpp"
 
 namespace sph {
 namespace {
@@ -104,10 +105,51 @@ __global__ __launch_bounds__(kBlock) void k_pairs64(GridDev g, int64_t n, Consts
                             p5.y + b5.y, p6.x + b6.x, p6.y + b6.y, b7.x, b3.y, acc, Ta, Tb, tens_a,
                             c_a, b7.y);
     });
-    postpass(k, io_index(g, s), rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs, st, out,
-             kCorr ? acc.M : nullptr);
+    postpass(k, io_index(g, s), rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs,
+             stress_of(st, io_index(g, s)).s, out, kCorr ? acc.M : nullptr);
     if (kExt) postpass_ext(k, io_index(g, s), acc, st, out);
     if (Lout) store_vgrad<kCorr>(Lout, s, acc.L, acc.M);
+}
+
+// The sums of the P wavefronts of a list kernel's workgroup added into wavefront 0
+// (fold_fields); the correction's and the extra terms' sums only where they are formed.
+template <int P, int Cap, bool kCorr, bool kExt>
+__device__ inline void fold_acc64(Acc64 &a, double *scratch) {
+    constexpr int F = 13 + (kCorr ? 6 : 0) + (kExt ? 4 : 0);
+    double v[F];
+    int i = 0;
+    v[i++] = a.rs;
+#pragma unroll
+    for (int c = 0; c < 9; ++c) v[i++] = a.L[c];
+    v[i++] = a.ax;
+    v[i++] = a.ay;
+    v[i++] = a.az;
+    if constexpr (kCorr) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) v[i++] = a.M[c];
+    }
+    if constexpr (kExt) {
+        v[i++] = a.du;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[i++] = a.xs[c];
+    }
+    fold_fields<P, Cap>(v, scratch);
+    i = 0;
+    a.rs = v[i++];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) a.L[c] = v[i++];
+    a.ax = v[i++];
+    a.ay = v[i++];
+    a.az = v[i++];
+    if constexpr (kCorr) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) a.M[c] = v[i++];
+    }
+    if constexpr (kExt) {
+        a.du = v[i++];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a.xs[c] = v[i++];
+    }
 }
 
 // FP64 pair sums over the frozen pair list: a workgroup of kSplit wavefronts takes one
@@ -172,10 +214,124 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs64_list(GridDev g, int64_t
     }
     fold_acc64<kSplit, kSplit * 64 * 16, kCorr, kExt>(acc, reinterpret_cast<double *>(lbuf));
     if (q != 0 || !act) return;
-    postpass(k, io_index(g, s), rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs, st, out,
+    const int a = io_index(g, s);
+    postpass(k, a, rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs, stress_of(st, a).s, out,
              kCorr ? acc.M : nullptr);
-    if (kExt) postpass_ext(k, io_index(g, s), acc, st, out);
+    if (kExt) postpass_ext(k, a, acc, st, out);
     if (Lout) store_vgrad<kCorr>(Lout, s, acc.L, acc.M);
+}
+
+// The same for a list with a skin, which is built to serve many evaluations and carries
+// hints (window.hpp): a block's partner records stand in the workgroup's LDS window, each
+// loaded once instead of once per slot that names it.  The window holds the first seven
+// chunks of a record (a partner's mass is V rho) and, with the extended terms, its sound
+// speed; wavefront q takes every kFwdWaves-th chunk of four steps, whose records are read
+// from LDS one step ahead.  The kernel above is bound by its gathers (the texture
+// addresser takes 64 B a clock and CU at best: 112 B a pair), this one by the pairs' FP64
+// arithmetic and LDS reads (118 and 73 cycles a step and CU): 262,144 particles with a
+// skin of 0.15 spacings 172 us of gathers, 121 here; with the extended terms 222 and 162;
+// two workgroups a CU are enough, since a step waits for no memory.
+// Without a skin the hints are not built: they cost 83 us on 262,144 particles, more than
+// the 51 us of one evaluation, and such a list holds for one set of positions only.
+constexpr int kFwdWaves = 4;
+
+template <bool kCorr, bool kExt>
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g, int64_t n, Consts k,
+                                                                   const double *__restrict__ rec,
+                                                                   StateDev st, OutDev out,
+                                                                   double *__restrict__ Lout) {
+    constexpr int W = kExt ? 640 : 704;  // two workgroups per CU
+    __shared__ double2 ring[W * 7];
+    __shared__ double cs[kExt ? W : 1];
+    __shared__ int32_t tag[W];
+    const int64_t w = xcd_block(gridDim.x);
+    const int64_t w0 = w * 64;
+    if (w0 >= n) return;  // whole workgroup past the end
+    const int64_t s = w0 + __lane_id();
+    const bool act = s < n;
+    const auto ahead = list_ahead<kFwdWaves, W>(g, w, s, act);
+    const double2 *ra = rec2(rec, act ? s : w0);
+    const double2 p0 = ra[0], p1 = ra[1], p2 = ra[2], p3 = ra[3], p4 = ra[4], p5 = ra[5],
+                  p6 = ra[6], p7 = ra[7];
+    const bool first = threadIdx.x < 64 && act;
+    const int a = first ? io_index(g, s) : 0;
+    Stress S;  // for the postpass, asked for ahead of the sweep
+    const ListBlock v = list_block(ahead);
+    const double xa = p0.x, ya = p0.y, za = p1.x, vxa = p1.y, vya = p2.x, vza = p2.y;
+    const double rho_a = p3.x;
+    Acc64 acc;
+    if (threadIdx.x < 64) acc.rs = p7.x * k.Wn;  // own term m_a W(0), once
+    const double c_a = p7.y;
+    const double Ta[6] = {p4.x, p4.y, p5.x, p5.y, p6.x, p6.y};
+    const bool tens_a = kExt && signbit(c_a);
+    const char *recs = reinterpret_cast<const char *>(rec);
+    struct Partner {
+        double2 b[7];
+        double c;
+        int32_t tag;
+    };
+    auto ready = [&] {
+        if (first) S = stress_of(st, a);
+    };
+    auto use = [&](int j, int t, Partner &r) {
+        const bool on = j < v.cnt;
+        if (__builtin_expect(__ballot(on && r.tag != t) != 0, 0)) {
+            if (on) {
+                const double2 *m = rec2(rec, t);
+#pragma unroll
+                for (int i = 0; i < 7; ++i) r.b[i] = m[i];
+                if constexpr (kExt) r.c = m[7].y;
+            }
+            wait_vm();  // here, or every step would wait for its prefetch
+        }
+        const double2 b0 = r.b[0], b1 = r.b[1], b2 = r.b[2], b3 = r.b[3], b4 = r.b[4], b5 = r.b[5],
+                      b6 = r.b[6];
+        const double d2 = dist2_exact(xa, ya, za, b0.x, b0.y, b1.x);
+        if (on && d2 < k.h2) {
+            const double Tb[6] = {b4.x, b4.y, b5.x, b5.y, b6.x, b6.y};
+            pair64<kCorr, kExt>(k, d2, xa - b0.x, ya - b0.y, za - b1.x, b1.y - vxa, b2.x - vya,
+                                b2.y - vza, rho_a, b3.x, p4.x + b4.x, p4.y + b4.y, p5.x + b5.x,
+                                p5.y + b5.y, p6.x + b6.x, p6.y + b6.y, b3.y * b3.x, b3.y, acc, Ta,
+                                Tb, tens_a, c_a, r.c);
+        }
+    };
+    if (v.locals) {
+        sweep_window(
+            v, ahead, tag, n,
+            [&](int p, int e) {
+                gather_dma<7>(recs, kRec * 8, e, ring + p * 64 * 7);
+                if constexpr (kExt) cs[64 * p + __lane_id()] = rec2(rec, e)[7].y;
+            },
+            ready,
+            [&](int at) {
+                Partner r;
+#pragma unroll
+                for (int i = 0; i < 7; ++i) r.b[i] = ring[7 * at + i];
+                r.c = kExt ? cs[at] : 0.0;
+                r.tag = tag[at];
+                return r;
+            },
+            use);
+    } else {
+        ready();
+        double2 *buf = ring + (threadIdx.x >> 6) * 64 * 8;
+        sweep_gather<kFwdWaves>(
+            v, [&](int e) { gather_dma8(recs, kRec * 8, e, buf); },
+            [&] {
+                Partner r;
+#pragma unroll
+                for (int i = 0; i < 7; ++i) r.b[i] = dma8_chunk(buf, i);
+                r.c = kExt ? dma8_chunk(buf, 7).y : 0.0;
+                return r;
+            },
+            use);
+    }
+    fold_acc64<kFwdWaves, W * 14, kCorr, kExt>(acc, reinterpret_cast<double *>(ring));
+    if (first) {
+        postpass(k, a, rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs, S.s, out, kCorr ? acc.M : nullptr);
+        if (kExt) postpass_ext(k, a, acc, st, out);
+        if (Lout) store_vgrad<kCorr>(Lout, s, acc.L, acc.M);
+    }
 }
 
 // ----------------------------------------- pairs, FP32 + Kahan sums --
@@ -239,8 +395,8 @@ __device__ inline Acc64 sums_of(const Acc32 &acc) {
 
 template <bool kCorr, bool kExt>
 __device__ inline void post32(const Consts &k, int a, double rho_a, double m_a, const Acc64 &acc,
-                              const StateDev &st, const OutDev &out, double *Lout, int64_t n,
-                              int64_t s) {
+                              const Stress &S, const StateDev &st, const OutDev &out, double *Lout,
+                              int64_t n, int64_t s) {
     if constexpr (kExt) {
         if (out.du) out.du[a] = 0.5 * acc.du;
         if (out.dx) {
@@ -250,7 +406,7 @@ __device__ inline void post32(const Consts &k, int a, double rho_a, double m_a, 
         }
     }
     const double rs = m_a * k.Wn + acc.rs;
-    postpass(k, a, rho_a, acc.L, acc.ax, acc.ay, acc.az, rs, st, out, kCorr ? acc.M : nullptr);
+    postpass(k, a, rho_a, acc.L, acc.ax, acc.ay, acc.az, rs, S.s, out, kCorr ? acc.M : nullptr);
     if (Lout) store_vgrad<kCorr>(Lout, s, acc.L, acc.M);
 }
 
@@ -270,8 +426,8 @@ __global__ __launch_bounds__(kBlock) void k_pairs32(GridDev g, int64_t n, Consts
         const double d2 = dist2_exact(a.x, a.y, a.z, b.x, b.y, b.z);
         if (d2 < k.h2) pair32_of<kCorr, kExt>(kf, a, b, d2, acc);
     });
-    post32<kCorr, kExt>(k, io_index(g, s), p3.x, p7.x, sums_of<kCorr, kExt>(acc), st, out, Lout, n,
-                        s);
+    post32<kCorr, kExt>(k, io_index(g, s), p3.x, p7.x, sums_of<kCorr, kExt>(acc),
+                        stress_of(st, io_index(g, s)), st, out, Lout, n, s);
 }
 
 // FP32 pair sums over the frozen pair list (cooperative gathers of the 80-byte records)
@@ -320,7 +476,8 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs32_list(GridDev g, int64_t
     fold_acc64<kSplit, kSplit * 64 * 5 * 2, kCorr, kExt>(sums, reinterpret_cast<double *>(lbuf));
     if (q != 0 || !act) return;
     const double2 p3 = rec2(rec, s)[3], p7 = rec2(rec, s)[7];
-    post32<kCorr, kExt>(k, io_index(g, s), p3.x, p7.x, sums, st, out, Lout, n, s);
+    const int ia = io_index(g, s);
+    post32<kCorr, kExt>(k, ia, p3.x, p7.x, sums, stress_of(st, ia), st, out, Lout, n, s);
 }
 
 }  // namespace
@@ -442,9 +599,12 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
         const dim3 gb(blocks_for(n)), tb(kBlock);
         auto launch = [&](auto corr, auto extra) {
             constexpr bool C = decltype(corr)::value, E = decltype(extra)::value;
-            if (g.pl_count)
+            if (g.pl_count && grid->pairs->skin > 0.0)
+                k_pairs64_window<C, E><<<blocks_for(n, 64), 64 * kFwdWaves, 0, s>>>(g, n, k, rec, st,
+                                                                                   od, L_out);
+            else if (g.pl_count)
                 k_pairs64_list<C, E><<<blocks_for(n, 64), 64 * kSplit, 0, s>>>(g, n, k, rec, st, od,
-                                                                             L_out);
+                                                                               L_out);
             else
                 k_pairs64<C, E><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out);
         };
@@ -467,8 +627,8 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
         auto launch = [&](auto corr, auto extra) {
             constexpr bool C = decltype(corr)::value, E = decltype(extra)::value;
             if (g.pl_count)
-                k_pairs32_list<C, E><<<blocks_for(n, 64), 64 * kSplit, 0, s>>>(g, n, k, rec, r32, st,
-                                                                             od, L_out);
+                k_pairs32_list<C, E><<<blocks_for(n, 64), 64 * kSplit, 0, s>>>(g, n, k, rec, r32,
+                                                                                 st, od, L_out);
             else
                 k_pairs32<C, E><<<gb, tb, 0, s>>>(g, n, k, rec, r32, st, od, L_out);
         };

@@ -582,47 +582,6 @@ struct Acc64 {
     double du = 0.0, xs[3] = {0, 0, 0};
 };
 
-// The sums of the P wavefronts of a list kernel's workgroup added into wavefront 0
-// (fold_waves); the correction's and the extra terms' sums only where they are formed.
-template <int P, int Cap, bool kCorr, bool kExt>
-__device__ inline void fold_acc64(Acc64 &a, double *scratch) {
-    constexpr int F = 13 + (kCorr ? 6 : 0) + (kExt ? 4 : 0);
-    double v[F];
-    int i = 0;
-    v[i++] = a.rs;
-#pragma unroll
-    for (int c = 0; c < 9; ++c) v[i++] = a.L[c];
-    v[i++] = a.ax;
-    v[i++] = a.ay;
-    v[i++] = a.az;
-    if constexpr (kCorr) {
-#pragma unroll
-        for (int c = 0; c < 6; ++c) v[i++] = a.M[c];
-    }
-    if constexpr (kExt) {
-        v[i++] = a.du;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) v[i++] = a.xs[c];
-    }
-    fold_waves<P, Cap>(v, scratch);
-    i = 0;
-    a.rs = v[i++];
-#pragma unroll
-    for (int c = 0; c < 9; ++c) a.L[c] = v[i++];
-    a.ax = v[i++];
-    a.ay = v[i++];
-    a.az = v[i++];
-    if constexpr (kCorr) {
-#pragma unroll
-        for (int c = 0; c < 6; ++c) a.M[c] = v[i++];
-    }
-    if constexpr (kExt) {
-        a.du = v[i++];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) a.xs[c] = v[i++];
-    }
-}
-
 // f^n for a fractional exponent, out of line so that the pair loop does not carry
 // the registers of pow
 __device__ __attribute__((noinline)) inline double pow_frac(double f, double n) { return pow(f, n); }
@@ -834,15 +793,22 @@ __device__ inline void corrected_gradient(const double L[9], const double M[6], 
             Lc[3 * i + j] = L[3 * i] * C[j] + L[3 * i + 1] * C[3 + j] + L[3 * i + 2] * C[6 + j];
 }
 
+struct Stress {
+    double s[6];
+};
+
+__device__ inline Stress stress_of(const StateDev &st, int a) {
+    return Stress{{st.sxx[a], st.syy[a], st.szz[a], st.sxy[a], st.sxz[a], st.syz[a]}};
+}
+
 // Stress rate (Hooke + Jaumann, section 2.4) and continuity for user particle a
-// from its velocity gradient L (L[3 i + j] = dv_i / dx_j), written with the
-// other outputs.  S~ = f_Y S;  dS = 2 mu (sym L - tr L / 3 I) + R S~ - S~ R.
+// from its stress S (before the limiter) and its velocity gradient L (L[3 i + j] =
+// dv_i / dx_j), written with the other outputs.  S~ = f_Y S;  dS = 2 mu (sym L - tr L / 3 I) + R S~ - S~ R.
 // With M (the correction's moment matrix), the strain and rotation rates use
 // L C; the continuity equation keeps tr L.
 __device__ inline void postpass(const Consts &k, int a, double rho, const double L0[9], double ax,
-                                double ay, double az, double rs, const StateDev &st,
+                                double ay, double az, double rs, const double S[6],
                                 const OutDev &o, const double *M = nullptr) {
-    double S[6] = {st.sxx[a], st.syy[a], st.szz[a], st.sxy[a], st.sxz[a], st.syz[a]};
     const double f = yield_factor(k, S);
     const double sa = f * S[0], sb = f * S[1], sc = f * S[2];
     const double sd = f * S[3], se = f * S[4], sf = f * S[5];

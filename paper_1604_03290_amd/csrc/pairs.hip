@@ -13,35 +13,13 @@
 // the one pass that tests and writes the candidates, so no count pass is needed.
 #include "common.hpp"
 #include "rhs_common.hpp"
+#include "sweep.hpp"
 #include "window.hpp"
 
 namespace sph {
 namespace {
 
 constexpr int kWave = 64;
-
-// Distance from the interval [b0, b1] to the slab of cell i along one axis (the
-// first and last cells extend to infinity, as in slab_gap).
-__device__ inline double box_gap(double b0, double b1, double lo, double cell, int i, int ncell) {
-    const double a = lo + cell * i;
-    const double b = a + cell;
-    double g = 0.0;
-    if (i > 0 && b1 < a) g = a - b1;
-    if (i < ncell - 1 && b0 > b) g = b0 - b;
-    return g;
-}
-
-__device__ inline double wave_min(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-    return v;
-}
-
-__device__ inline double wave_max(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    return v;
-}
 
 // Gathers the positions into slot order and bounds every slot's candidates: the slots of
 // the cells within reach of its position (each candidate lies in one of them, within delta
@@ -87,10 +65,8 @@ __global__ __launch_bounds__(kBlock) void k_pl_bound(GridDev g, const double *__
 // box widened by the radius (one farther away is no lane's candidate); the survivors
 // are packed in order into an LDS buffer, which the 64 lanes test against their own
 // slots 64 candidates at a time (broadcast reads).  A group spread over a region of
-// more than kSpread times one slot's cells (sparse parts of a set) sweeps per lane
-// instead, in the order of for_each_row.
-constexpr double kSpread = 8.0;
-constexpr int kRunCap = 256;  // runs of one pass (LDS)
+// more than kSpread times one slot's cells sweeps tile by tile, or per lane, in the order
+// of for_each_row either way.
 
 __global__ __launch_bounds__(kBlock) void k_pl_fill(GridDev g, const double *__restrict__ x0,
                                                     int64_t n, double r2, double reach,
@@ -126,28 +102,22 @@ __global__ __launch_bounds__(kBlock) void k_pl_fill(GridDev g, const double *__r
         np += d < h2;
         ++c;
     };
-    const double bx0 = wave_min(xa), bx1 = wave_max(xa);
-    const double by0 = wave_min(ya), by1 = wave_max(ya);
-    const double bz0 = wave_min(za), bz1 = wave_max(za);
-    const int z0 = cell_index(bz0 - reach, g.loz, g.inv_cell, g.nz);
-    const int z1 = cell_index(bz1 + reach, g.loz, g.inv_cell, g.nz);
-    const int y0 = cell_index(by0 - reach, g.loy, g.inv_cell, g.ny);
-    const int y1 = cell_index(by1 + reach, g.loy, g.inv_cell, g.ny);
-    const int x0c = cell_index(bx0 - reach, g.lox, g.inv_cell, g.nx);
-    const int x1c = cell_index(bx1 + reach, g.lox, g.inv_cell, g.nx);
-    const double own = 2.0 * reach * g.inv_cell + 1.0;  // cells along one axis of one slot
-    const double box = (double)(x1c - x0c + 1) * (y1 - y0 + 1) * (z1 - z0 + 1);
-    if (box > kSpread * own * own * own) {
-        if (act)
-            for_each_row(g, xa, ya, za, reach, [&](int s0, int s1) {
-                for (int t = s0; t < s1; ++t) {
-                    if (t == s) continue;
-                    const double d = dist2_exact(xa, ya, za, x0[3 * t], x0[3 * t + 1], x0[3 * t + 2]);
-                    if (d < r2) hit(t, d);
-                }
-            });
-    } else {
-        const double rr = reach * reach;
+    GroupParts parts(g, act, sa, xa, ya, za, reach);
+    while (parts.todo) {
+        bool single;
+        const bool in = parts.next(g, act, xa, ya, za, reach, single);
+        const GroupBox &box = parts.box;
+        if (single) {
+            if (in)
+                for_each_row(g, xa, ya, za, reach, [&](int s0, int s1) {
+                    for (int t = s0; t < s1; ++t) {
+                        if (t == s) continue;
+                        const double d = dist2_exact(xa, ya, za, x0[3 * t], x0[3 * t + 1], x0[3 * t + 2]);
+                        if (d < r2) hit(t, d);
+                    }
+                });
+            continue;
+        }
         // the cull keeps every candidate within the radius of a point of the box, with a
         // margin far above the rounding of either distance
         const double rb2 = r2 * (1.0 + 1e-6);
@@ -164,12 +134,12 @@ __global__ __launch_bounds__(kBlock) void k_pl_fill(GridDev g, const double *__r
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (act && d[q] < r2 && t[q] != (int)s) hit(t[q], d[q]);
+                    if (in && d[q] < r2 && t[q] != (int)s) hit(t[q], d[q]);
             }
             for (; k < m; ++k) {
                 const int t = cand_t[k];
                 const double d = dist2_exact(xa, ya, za, cand[0][k], cand[1][k], cand[2][k]);
-                if (act && d < r2 && t != (int)s) hit(t, d);
+                if (in && d < r2 && t != (int)s) hit(t, d);
             }
         };
         // one candidate per lane (t, where valid): loaded, culled, packed behind the
@@ -181,10 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_pl_fill(GridDev g, const double *__r
                 px = x0[3 * (int64_t)t];
                 py = x0[3 * (int64_t)t + 1];
                 pz = x0[3 * (int64_t)t + 2];
-                const double ex = fmax(fmax(bx0 - px, px - bx1), 0.0);
-                const double ey = fmax(fmax(by0 - py, py - by1), 0.0);
-                const double ez = fmax(fmax(bz0 - pz, pz - bz1), 0.0);
-                keep = ex * ex + ey * ey + ez * ez < rb2;
+                keep = box.dist2(px, py, pz) < rb2;
             }
             const unsigned long long mk = __ballot(keep);
             if (keep) {
@@ -210,105 +177,16 @@ __global__ __launch_bounds__(kBlock) void k_pl_fill(GridDev g, const double *__r
                 wave_sync();
             }
         };
-        // rows from the middle of the region outwards (z, then y): the lanes of the
-        // group then meet their partners at more even rates, so that the rows of the
-        // list they fill together are completed sooner.  Row rank r: z the r / ny-th
-        // and y the r % ny-th of that order.
-        const int nzr = z1 - z0 + 1, nyr = y1 - y0 + 1, nrows = nzr * nyr;
-        auto middle_out = [](int r, int lo, int hi) {  // r-th of c, c - 1, c + 1, c - 2, ...
-            const int c = (lo + hi) >> 1, a = c - lo;
-            return r <= 2 * a ? c + ((r & 1) ? -((r + 1) >> 1) : (r >> 1)) : hi;
-        };
-        for (int rb = 0; rb < nrows;) {
-            // this lane's row of the pass: its cells in x and its number of runs
-            const int r = rb + lane;
-            int iy = 0, iz = 0, xr0 = 0, xr1 = -1, nr = 0;
-            if (r < nrows) {
-                iz = middle_out(r / nyr, z0, z1);
-                iy = middle_out(r % nyr, y0, y1);
-                const double gz = box_gap(bz0, bz1, g.loz, g.cell, iz, g.nz);
-                const double gy = box_gap(by0, by1, g.loy, g.cell, iy, g.ny);
-                const double d2 = gz * gz + gy * gy;
-                if (gz * gz < rr && d2 < rr) {
-                    const double w = sqrt(rr - d2) * (1.0 + 1e-9);
-                    xr0 = cell_index(bx0 - w, g.lox, g.inv_cell, g.nx);
-                    xr1 = cell_index(bx1 + w, g.lox, g.inv_cell, g.nx);
-                    for_each_cell_run(g, iy, iz, xr0, xr1, [&](int, int) { ++nr; });
-                }
-            }
-            // runs before this lane's (exclusive scan over the lanes)
-            int off = nr;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int v = __shfl_up(off, o);
-                if (lane >= o) off += v;
-            }
-            off -= nr;
-            // the rows that fit the pass: a prefix of the lanes
-            const int take = __popcll(__ballot(r < nrows && off + nr <= kRunCap));
-            if (take == 0) {
-                // a single row with more runs than a pass holds: its runs one by one
-                const int fy = __builtin_amdgcn_readfirstlane(iy), fz = __builtin_amdgcn_readfirstlane(iz);
-                const int f0 = __builtin_amdgcn_readfirstlane(xr0), f1 = __builtin_amdgcn_readfirstlane(xr1);
-                for_each_run(g, fy, fz, f0, f1, [&](int s0, int s1) {
-                    for (int t0 = s0; t0 < s1; t0 += kWave) push(t0 + lane < s1, t0 + lane);
-                });
-                rb += 1;
-                continue;
-            }
-            const int nrun = __shfl(off + nr, take - 1);
-            if (lane < take && nr > 0) {  // (a culled row has no runs)
-                int j = off;
-                for_each_cell_run(g, iy, iz, xr0, xr1, [&](int c0, int c1) {
-                    run_s0[j] = c0;
-                    run_pre[j] = c1;
-                    ++j;
-                });
-            }
+        const int nrows = box.rows();
+        for (int rb = 0, skip = 0; rb < nrows;) {
+            const RunPass p = lay_runs(g, box, parts.tiles == 0, reach, rb, skip, run_s0, run_pre);
+            // the pass's candidates in order, 64 at a time
+            for (int f0 = 0; f0 < p.total; f0 += kWave)
+                push(f0 + lane < p.total, slot_of_run(f0 + lane, p.runs, run_s0, run_pre));
             wave_sync();
-            // the runs' slots: cells to slot ranges, and their lengths scanned
-            int len[kRunCap / kWave], sum = 0;
-#pragma unroll
-            for (int q = 0; q < kRunCap / kWave; ++q) {
-                const int j = kRunCap / kWave * lane + q;
-                len[q] = 0;
-                if (j < nrun) {
-                    const int s0 = g.cell_start[run_s0[j]];
-                    len[q] = g.cell_start[run_pre[j]] - s0;
-                    run_s0[j] = s0;
-                }
-                sum += len[q];
-            }
-            int before = sum;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int v = __shfl_up(before, o);
-                if (lane >= o) before += v;
-            }
-            const int total = __shfl(before, 63);
-            before -= sum;
-#pragma unroll
-            for (int q = 0; q < kRunCap / kWave; ++q) {
-                const int j = kRunCap / kWave * lane + q;
-                if (j < nrun) run_pre[j] = before;
-                before += len[q];
-            }
-            wave_sync();
-            // the pass's candidates in order, 64 at a time (run of candidate f: the last
-            // with run_pre <= f)
-            for (int f0 = 0; f0 < total; f0 += kWave) {
-                const int f = f0 + lane;
-                int lo = 0, hi = nrun;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (run_pre[mid] <= f) lo = mid; else hi = mid;
-                }
-                push(f < total, run_s0[lo] + (f - run_pre[lo]));
-            }
-            wave_sync();
-            rb += take;
         }
         test(pend);
+        wave_sync();
     }
     // the group's steps: its longest list (at most its room)
     int steps = min((int64_t)c, room);

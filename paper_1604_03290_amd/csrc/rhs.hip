@@ -22,6 +22,7 @@
 #include "common.hpp"
 #include "rhs_common.hpp"
 #include "timing.hpp"
+#include "sweep.hpp"
 #include "window.hpp"
 
 namespace sph {
@@ -78,39 +79,6 @@ __global__ __launch_bounds__(kBlock) void k_narrow(const double *__restrict__ re
 }
 
 // ---------------------------------------------------------- pairs, FP64 --
-template <bool kCorr, bool kExt>
-__global__ __launch_bounds__(kBlock) void k_pairs64(GridDev g, int64_t n, Consts k,
-                                                    const double *__restrict__ rec, StateDev st,
-                                                    OutDev out, double *__restrict__ Lout) {
-    const int64_t s = xcd_block(gridDim.x) * kBlock + threadIdx.x;
-    if (s >= n) return;
-    const double2 *ra = rec2(rec, s);
-    const double2 p0 = ra[0], p1 = ra[1], p2 = ra[2], p3 = ra[3], p4 = ra[4], p5 = ra[5], p6 = ra[6];
-    const double xa = p0.x, ya = p0.y, za = p1.x, vxa = p1.y, vya = p2.x, vza = p2.y;
-    const double rho_a = p3.x;
-    Acc64 acc;
-    acc.rs = ra[7].x * k.Wn;  // own term m_a W(0)
-    const double c_a = ra[7].y;
-    const double Ta[6] = {p4.x, p4.y, p5.x, p5.y, p6.x, p6.y};
-    const bool tens_a = kExt && signbit(c_a);
-    for_each_candidate(g, s, xa, ya, za, k.reach, [&](int t) {
-        const double2 *rb = rec2(rec, t);
-        const double2 b0 = rb[0], b1 = rb[1];
-        const double d2 = dist2_exact(xa, ya, za, b0.x, b0.y, b1.x);
-        if (!(d2 < k.h2)) return;
-        const double2 b2 = rb[2], b3 = rb[3], b4 = rb[4], b5 = rb[5], b6 = rb[6], b7 = rb[7];
-        const double Tb[6] = {b4.x, b4.y, b5.x, b5.y, b6.x, b6.y};
-        pair64<kCorr, kExt>(k, d2, xa - b0.x, ya - b0.y, za - b1.x, b1.y - vxa, b2.x - vya,
-                            b2.y - vza, rho_a, b3.x, p4.x + b4.x, p4.y + b4.y, p5.x + b5.x,
-                            p5.y + b5.y, p6.x + b6.x, p6.y + b6.y, b7.x, b3.y, acc, Ta, Tb, tens_a,
-                            c_a, b7.y);
-    });
-    postpass(k, io_index(g, s), rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs,
-             stress_of(st, io_index(g, s)).s, out, kCorr ? acc.M : nullptr);
-    if (kExt) postpass_ext(k, io_index(g, s), acc, st, out);
-    if (Lout) store_vgrad<kCorr>(Lout, s, acc.L, acc.M);
-}
-
 // The sums of the P wavefronts of a list kernel's workgroup added into wavefront 0
 // (fold_fields); the correction's and the extra terms' sums only where they are formed.
 template <int P, int Cap, bool kCorr, bool kExt>
@@ -332,6 +300,235 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g,
         if (kExt) postpass_ext(k, a, acc, st, out);
         if (Lout) store_vgrad<kCorr>(Lout, s, acc.L, acc.M);
     }
+}
+
+// FP64 pair sums straight from the cells: a workgroup of kCellWaves wavefronts takes 64
+// slots, in the parts of sweep.hpp.  Their candidates, the slots of the cells around a
+// part's box, are culled one per thread against the box widened by h and dealt to the
+// wavefronts in turn, each of which has room for kOwn records in LDS; when these are full,
+// or the candidates at an end, the records are loaded, each wavefront tests its own for
+// all 64 slots (broadcast reads, one bit per candidate and slot) and every slot evaluates
+// the partners it was left, whichever they are.  So a step of the evaluation idles only
+// the slots that have run out of partners (a lane walking its own slot's cells is idle at
+// three candidates of four, some other lane's partners), and a small set still has a
+// workgroup per 64 slots.  The tests (12 instructions per candidate and 64 slots) and the
+// evaluation each bound it about as much as the search for candidates does.  One slot per
+// lane in workgroups of 256 took 234 us on 4,096 particles and 309 us on 110,592; this
+// takes 45 and 185, and with the extended terms 364 us are now 240.
+constexpr int kCellWaves = 4;
+
+template <bool kCorr, bool kExt>
+__global__ __launch_bounds__(64 * kCellWaves, 2) void k_pairs64_cells(GridDev g, int64_t n, Consts k,
+                                                                  const double *__restrict__ rec,
+                                                                  StateDev st, OutDev out,
+                                                                  double *__restrict__ Lout) {
+    constexpr int P = kCellWaves, kOwn = 160, W = P * kOwn;  // two workgroups per CU
+    constexpr int kBlocks = W / 64, kMine = (kBlocks + P - 1) / P;
+    __shared__ double2 ring[W * 7];
+    __shared__ double cs[kExt ? W : 1];
+    __shared__ int32_t tag[W];
+    __shared__ int32_t run_s0[kRunCap], run_pre[kRunCap];
+    __shared__ int32_t pass[4], kept[2][P];
+    __shared__ int32_t self[64];  // places of the group's own slots, -1: not there
+    const int lane = __lane_id();
+    const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t w0 = xcd_block(gridDim.x) * 64;
+    if (w0 >= n) return;  // whole workgroup past the end
+    const int64_t s = w0 + lane;
+    const bool act = s < n;
+    const double2 *ra = rec2(rec, act ? s : w0);  // lanes past n stand on the group's first slot
+    const double2 p0 = ra[0], p1 = ra[1], p2 = ra[2], p3 = ra[3], p4 = ra[4], p5 = ra[5],
+                  p6 = ra[6], p7 = ra[7];
+    const double xa = p0.x, ya = p0.y, za = p1.x, vxa = p1.y, vya = p2.x, vza = p2.y;
+    const double rho_a = p3.x;
+    Acc64 acc;
+    if (q == 0) acc.rs = p7.x * k.Wn;  // own term m_a W(0), once
+    const double c_a = p7.y;
+    const double Ta[6] = {p4.x, p4.y, p5.x, p5.y, p6.x, p6.y};
+    const bool tens_a = kExt && signbit(c_a);
+    struct Partner {
+        double2 b[7];
+        double c;
+    };
+    auto use = [&](const Partner &r, bool on) {
+        const double2 b0 = r.b[0], b1 = r.b[1], b2 = r.b[2], b3 = r.b[3], b4 = r.b[4], b5 = r.b[5],
+                      b6 = r.b[6];
+        const double d2 = dist2_exact(xa, ya, za, b0.x, b0.y, b1.x);
+        if (on && d2 < k.h2) {
+            const double Tb[6] = {b4.x, b4.y, b5.x, b5.y, b6.x, b6.y};
+            pair64<kCorr, kExt>(k, d2, xa - b0.x, ya - b0.y, za - b1.x, b1.y - vxa, b2.x - vya,
+                                b2.y - vza, rho_a, b3.x, p4.x + b4.x, p4.y + b4.y, p5.x + b5.x,
+                                p5.y + b5.y, p6.x + b6.x, p6.y + b6.y, b3.y * b3.x, b3.y, acc, Ta,
+                                Tb, tens_a, c_a, r.c);
+        }
+    };
+    GroupParts parts(g, act, act ? s : w0, xa, ya, za, k.reach);
+    while (parts.todo) {
+        bool single;
+        const bool in = parts.next(g, act, xa, ya, za, k.reach, single);
+        const GroupBox &box = parts.box;
+        if (single) {  // slot by slot, every P-th candidate a wavefront's
+            int i = 0;
+            if (in)
+                for_each_row(g, xa, ya, za, k.reach, [&](int s0, int s1) {
+                    for (int t = s0; t < s1; ++t) {
+                        if (t == s || (i++ & (P - 1)) != q) continue;
+                        const double2 *rb = rec2(rec, t);
+                        Partner r;
+                        r.b[0] = rb[0];
+                        r.b[1] = rb[1];
+                        if (!(dist2_exact(xa, ya, za, r.b[0].x, r.b[0].y, r.b[1].x) < k.h2)) continue;
+#pragma unroll
+                        for (int c = 2; c < 7; ++c) r.b[c] = rb[c];
+                        r.c = kExt ? rb[7].y : 0.0;
+                        use(r, true);
+                    }
+                });
+            continue;
+        }
+        // the m candidates in tag: candidate i is wavefront i mod P's, at its place i / P
+        auto evaluate = [&](int m) {
+            if (q == 0) self[lane] = -1;
+            __syncthreads();
+            int e[kMine];
+            bool any[kMine];
+#pragma unroll
+            for (int i = 0; i < kMine; ++i) {
+                const int at = 64 * (q + i * P) + lane;
+                const bool there = at < W && P * (at % kOwn) + at / kOwn < m;
+                e[i] = there ? tag[at] : (int)w0;
+                any[i] = __ballot(there) != 0;
+                if (there && (uint32_t)(e[i] - (int)w0) < 64u) self[e[i] - (int)w0] = at;
+            }
+#pragma unroll
+            for (int i = 0; i < kMine; ++i)
+                if (any[i]) {
+                    const int b = q + i * P;
+                    gather_dma<7>(reinterpret_cast<const char *>(rec), kRec * 8, e[i], ring + b * 64 * 7);
+                    if constexpr (kExt) cs[64 * b + lane] = rec2(rec, e[i])[7].y;
+                }
+            wait_vm();
+            __syncthreads();
+            const int mq = m > q ? (m - q + P - 1) / P : 0;
+            const double2 *own = ring + q * kOwn * 7;
+            uint64_t left[3] = {0, 0, 0};  // this slot's partners among them
+            static_assert(kOwn > 128 && kOwn <= 192 && kOwn % 4 == 0, "three words of bits");
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                const int bits = min(mq - 64 * u, 64);
+                for (int b = 0; b < bits; b += 4) {  // four at a time: their reads overlap
+                    double2 b0[4];
+                    double z[4];
+                    uint32_t hit = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        b0[i] = own[7 * (64 * u + b + i)];
+                        z[i] = own[7 * (64 * u + b + i) + 1].x;
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        hit |= (uint32_t)(dist2_exact(xa, ya, za, b0[i].x, b0[i].y, z[i]) < k.h2) << i;
+                    left[u] |= (uint64_t)hit << b;
+                }
+                if (bits < 64) left[u] &= bits > 0 ? (1ull << bits) - 1 : 0;
+                const int me = self[lane] - q * kOwn - 64 * u;
+                if (me >= 0 && me < 64) left[u] &= ~(1ull << me);
+                if (!in) left[u] = 0;
+            }
+            int first = 0;  // candidate of bit 0 of left[0]
+            bool on;
+            auto fetch = [&] {  // the next partner (any record where there is none)
+                if (left[0] == 0) {
+                    left[0] = left[1];
+                    left[1] = left[2];
+                    left[2] = 0;
+                    first += 64;
+                }
+                if (left[0] == 0) {
+                    left[0] = left[1];
+                    left[1] = 0;
+                    first += 64;
+                }
+                on = left[0] != 0;
+                const int at = on ? first + __builtin_ctzll(left[0]) : 0;
+                left[0] &= left[0] - 1;
+                Partner r;
+#pragma unroll
+                for (int c = 0; c < 7; ++c) r.b[c] = own[7 * at + c];
+                r.c = kExt ? cs[q * kOwn + at] : 0.0;
+                return r;
+            };
+            Partner r = fetch();
+            while (__ballot(on)) {
+                if constexpr (kCorr || kExt) {  // (no registers for a record ahead)
+                    use(r, on);
+                    r = fetch();
+                } else {
+                    const bool now = on;
+                    const Partner then = fetch();
+                    use(r, now);
+                    r = then;
+                }
+            }
+            __syncthreads();
+        };
+        const double rb2 = k.h2 * (1.0 + 1e-6);  // far above the rounding of either distance
+        int pend = 0, parity = 0;
+        const int nrows = box.rows();
+        for (int rb = 0, skip = 0; rb < nrows;) {
+            if (q == 0) {
+                const RunPass p = lay_runs(g, box, parts.tiles == 0, k.reach, rb, skip, run_s0, run_pre);
+                if (lane == 0) {
+                    pass[0] = rb;
+                    pass[1] = skip;
+                    pass[2] = p.runs;
+                    pass[3] = p.total;
+                }
+            }
+            __syncthreads();
+            rb = pass[0];
+            skip = pass[1];
+            const int runs = pass[2], total = pass[3];
+            for (int f0 = 0; f0 < total; f0 += 64 * P) {
+                const int f = f0 + threadIdx.x;
+                bool keep = false;
+                int t = 0;
+                if (f < total) {
+                    t = slot_of_run(f, runs, run_s0, run_pre);
+                    const double2 b0 = rec2(rec, t)[0], b1 = rec2(rec, t)[1];
+                    keep = box.dist2(b0.x, b0.y, b1.x) < rb2;
+                }
+                const unsigned long long mk = __ballot(keep);
+                if (lane == 0) kept[parity][q] = __popcll(mk);
+                __syncthreads();
+                int at = pend, all = 0;
+#pragma unroll
+                for (int i = 0; i < P; ++i) {
+                    if (i < q) at += kept[parity][i];
+                    all += kept[parity][i];
+                }
+                parity ^= 1;  // (written again only after the next barrier)
+                at += __popcll(mk & ((1ull << lane) - 1));
+                auto put = [&](int i) { tag[i % P * kOwn + i / P] = t; };
+                if (keep && at < W) put(at);
+                pend += all;
+                if (pend >= W) {  // (fewer than W were waiting, at most 64 P <= W came)
+                    evaluate(W);
+                    if (keep && at >= W) put(at - W);
+                    pend -= W;
+                }
+            }
+            __syncthreads();  // the runs are overwritten next
+        }
+        evaluate(pend);
+    }
+    fold_acc64<P, W * 14, kCorr, kExt>(acc, reinterpret_cast<double *>(ring));
+    if (q != 0 || !act) return;
+    const int a = io_index(g, s);
+    postpass(k, a, rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs, stress_of(st, a).s, out,
+             kCorr ? acc.M : nullptr);
+    if (kExt) postpass_ext(k, a, acc, st, out);
+    if (Lout) store_vgrad<kCorr>(Lout, s, acc.L, acc.M);
 }
 
 // ----------------------------------------- pairs, FP32 + Kahan sums --
@@ -596,7 +793,6 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
     const bool ext = k.eps_s > 0.0 || od.du || od.dx || k.eos != 0;
     if (precision == SPH_FP64) {
         TimedRegion t(timed ? "pairs_fp64" : nullptr, s);
-        const dim3 gb(blocks_for(n)), tb(kBlock);
         auto launch = [&](auto corr, auto extra) {
             constexpr bool C = decltype(corr)::value, E = decltype(extra)::value;
             if (g.pl_count && grid->pairs->skin > 0.0)
@@ -606,7 +802,8 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
                 k_pairs64_list<C, E><<<blocks_for(n, 64), 64 * kSplit, 0, s>>>(g, n, k, rec, st, od,
                                                                                L_out);
             else
-                k_pairs64<C, E><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out);
+                k_pairs64_cells<C, E><<<blocks_for(n, 64), 64 * kCellWaves, 0, s>>>(g, n, k, rec, st,
+                                                                                   od, L_out);
         };
         using T = std::true_type;
         using F = std::false_type;

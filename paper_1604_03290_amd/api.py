@@ -36,6 +36,16 @@ def _ptr(t):
     return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
 
 
+def _rows(t: torch.Tensor, k: int) -> list:
+    """Addresses of t[0] .. t[k - 1], without a tensor for each (about 1 us; a forward and
+    backward pass takes 45 of them)."""
+    if t.shape[0] < k:
+        raise IndexError(f"expected {k} rows, got {tuple(t.shape)}")
+    p = t.data_ptr()
+    step = t.stride(0) * t.element_size() if p else 0
+    return [p + i * step for i in range(k)]
+
+
 def _dev(t: torch.Tensor, dtype=F64) -> torch.Tensor:
     if not t.is_cuda:
         raise ValueError("tensors must be on the GPU")
@@ -87,13 +97,10 @@ class ParticleState:
             _dev(self.flaw_ptr, torch.int64)
             _dev(self.flaw_eps)
             assert self.flaw_ptr.shape == (n + 1,)
-        p, v, s = self.pos, self.vel, self.S
         q = lambda t: t.data_ptr() if t is not None else None
-        return L.State(n, p[0].data_ptr(), p[1].data_ptr(), p[2].data_ptr(), v[0].data_ptr(),
-                       v[1].data_ptr(), v[2].data_ptr(), self.rho.data_ptr(), s[0].data_ptr(),
-                       s[1].data_ptr(), s[2].data_ptr(), s[3].data_ptr(), s[4].data_ptr(),
-                       s[5].data_ptr(), self.m.data_ptr(), q(self.u), q(self.d), q(self.flaw_ptr),
-                       q(self.flaw_eps))
+        return L.State(n, *_rows(self.pos, 3), *_rows(self.vel, 3), self.rho.data_ptr(),
+                       *_rows(self.S, 6), self.m.data_ptr(), q(self.u), q(self.d),
+                       q(self.flaw_ptr), q(self.flaw_eps))
 
 
 def params_struct(params) -> L.Params:
@@ -298,16 +305,13 @@ def deriv_struct(d: dict, cls=L.Deriv):
         _dev(t)
     rs = d.get("rho_sum")
     p = lambda t: t.data_ptr() if t is not None else None
-    args = [a[0].data_ptr(), a[1].data_ptr(), a[2].data_ptr(), d["drho"].data_ptr(),
-            s[0].data_ptr(), s[1].data_ptr(), s[2].data_ptr(), s[3].data_ptr(),
-            s[4].data_ptr(), s[5].data_ptr(), p(rs)]
+    args = [*_rows(a, 3), d["drho"].data_ptr(), *_rows(s, 6), p(rs)]
     if cls is L.Deriv:
         du, xv = d.get("du"), d.get("xv")
         for t in (du, xv):
             if t is not None:
                 _dev(t)
-        args += [p(du)] + ([xv[0].data_ptr(), xv[1].data_ptr(), xv[2].data_ptr()]
-                           if xv is not None else [None, None, None])
+        args += [p(du)] + (_rows(xv, 3) if xv is not None else [None, None, None])
         dd3, na = d.get("dd3"), d.get("n_act")
         if dd3 is not None:
             _dev(dd3)
@@ -324,10 +328,7 @@ def deriv_struct(d: dict, cls=L.Deriv):
 
 
 def fields_struct(pos, vel, rho, S, cls=L.Fields):
-    return cls(pos[0].data_ptr(), pos[1].data_ptr(), pos[2].data_ptr(), vel[0].data_ptr(),
-               vel[1].data_ptr(), vel[2].data_ptr(), rho.data_ptr(), S[0].data_ptr(),
-               S[1].data_ptr(), S[2].data_ptr(), S[3].data_ptr(), S[4].data_ptr(),
-               S[5].data_ptr())
+    return cls(*_rows(pos, 3), *_rows(vel, 3), rho.data_ptr(), *_rows(S, 6))
 
 
 def precision_code(precision) -> int:
@@ -347,14 +348,15 @@ def sph_rhs(grid: CellGrid, state: ParticleState, params, precision="fp64", out=
     with ``vgrad`` (FP64) the velocity gradient and with ``records`` the operand records
     (rec) that sph_rhs_adjoint can take back."""
     n = state.n
+    prm = params_struct(params)
     if out is None:
-        nv = (15 if params_struct(params).correction != 0.0 else 9) if vgrad else 0
+        nv = (15 if prm.correction != 0.0 else 9) if vgrad else 0
         out = new_deriv(n, state.rho.device, extra, damage, nv, records)
     if ws is None:
         ws = workspace(L.SPH_OP_RHS, n, 0, state.rho.device)
     cs = state.c_state()
     d = deriv_struct(out)
-    L.check(L.lib().sph_rhs(C.byref(grid.c), C.byref(cs), C.byref(params_struct(params)),
+    L.check(L.lib().sph_rhs(C.byref(grid.c), C.byref(cs), C.byref(prm),
                             precision_code(precision), C.byref(d), _ptr(ws), ws.numel(),
                             _stream()))
     out["_ws"] = ws
@@ -387,24 +389,33 @@ def sph_rhs_adjoint(grid: CellGrid, state: ParticleState, params, cot: dict,
     of forming the velocity gradient again; ``rec`` likewise its "rec" output (the
     operand records), reused instead of running the prepass again.  Returns gradients
     pos, vel, rho, S, mu, Y0, and u with the Tillotson equation."""
+    g, dparams, ws = _rhs_adjoint(grid, state, params, cot, ws, vgrad, rec)
+    g["mu"] = dparams[0]
+    g["Y0"] = dparams[1]
+    g["_ws"] = ws
+    return g
+
+
+def _rhs_adjoint(grid, state, params, cot, ws, vgrad, rec):
+    """sph_rhs_adjoint's gradients without mu and Y0, the tensor of these two, the workspace."""
     n = state.n
+    prm = params_struct(params)
     dev = state.rho.device
     z3 = lambda k, shape: _dev(cot[k]) if cot.get(k) is not None else None
     acc, drho, dS, rs = (z3("acc", None), z3("drho", None), z3("dS", None), z3("rho_sum", None))
     du, xv = z3("du", None), z3("xv", None)
-    p = lambda t, i=None: (t[i].data_ptr() if i is not None else t.data_ptr()) if t is not None else None
+    p = lambda t: t.data_ptr() if t is not None else None
+    r = lambda t, k: _rows(t, k) if t is not None else [None] * k
     if vgrad is not None:
         _dev(vgrad)
-        want = 15 if params_struct(params).correction != 0.0 else 9
+        want = 15 if prm.correction != 0.0 else 9
         if tuple(vgrad.shape) != (n, want) or not vgrad.is_contiguous():
             raise ValueError(f"vgrad must be contiguous ({n}, {want}), got {tuple(vgrad.shape)}")
     if rec is not None:
         _dev(rec)
         if tuple(rec.shape) != (n, REC_DOUBLES) or not rec.is_contiguous():
             raise ValueError(f"rec must be contiguous ({n}, {REC_DOUBLES}), got {tuple(rec.shape)}")
-    dc = L.DerivCot(p(acc, 0), p(acc, 1), p(acc, 2), p(drho), p(dS, 0), p(dS, 1), p(dS, 2),
-                    p(dS, 3), p(dS, 4), p(dS, 5), p(rs), p(du), p(xv, 0), p(xv, 1), p(xv, 2),
-                    p(vgrad), p(rec))
+    dc = L.DerivCot(*r(acc, 3), p(drho), *r(dS, 6), p(rs), p(du), *r(xv, 3), p(vgrad), p(rec))
     g = dict(pos=torch.empty(3, n, dtype=F64, device=dev), vel=torch.empty(3, n, dtype=F64, device=dev),
              rho=torch.empty(n, dtype=F64, device=dev), S=torch.empty(6, n, dtype=F64, device=dev))
     dparams = torch.empty(2, dtype=F64, device=dev)
@@ -412,16 +423,12 @@ def sph_rhs_adjoint(grid: CellGrid, state: ParticleState, params, cot: dict,
         ws = workspace(L.SPH_OP_ADJOINT, n, 0, dev)
     cs = state.c_state()
     fs = fields_struct(g["pos"], g["vel"], g["rho"], g["S"])
-    if params_struct(params).eos == 2.0:
+    if prm.eos == 2.0:
         g["u"] = torch.empty(n, dtype=F64, device=dev)
         fs.u = g["u"].data_ptr()
-    L.check(L.lib().sph_rhs_adjoint(C.byref(grid.c), C.byref(cs), C.byref(params_struct(params)),
-                                    C.byref(dc), C.byref(fs), _ptr(dparams), _ptr(ws), ws.numel(),
-                                    _stream()))
-    g["mu"] = dparams[0]
-    g["Y0"] = dparams[1]
-    g["_ws"] = ws
-    return g
+    L.check(L.lib().sph_rhs_adjoint(C.byref(grid.c), C.byref(cs), C.byref(prm), C.byref(dc),
+                                    C.byref(fs), _ptr(dparams), _ptr(ws), ws.numel(), _stream()))
+    return g, dparams, ws
 
 
 class SphRhs(torch.autograd.Function):
@@ -465,9 +472,12 @@ class SphRhs(torch.autograd.Function):
         st = ParticleState(c(pos), c(vel), c(rho), c(S), c(m), u=c(u), d=c(d))
         names = ("acc", "drho", "dS", "rho_sum", "du", "xv")
         cot = {k: (v.contiguous() if v is not None else None) for k, v in zip(names, grads)}
-        g = sph_rhs_adjoint(ctx.grid, st, ctx.params, cot, vgrad=ctx.vgrad, rec=ctx.rec)
-        gmu = g["mu"].to(ctx.mu_like.device, ctx.mu_like.dtype).reshape(ctx.mu_like.shape)
-        gY0 = g["Y0"].to(ctx.Y0_like.device, ctx.Y0_like.dtype).reshape(ctx.Y0_like.shape)
+        g, dparams, _ = _rhs_adjoint(ctx.grid, st, ctx.params, cot, None, ctx.vgrad, ctx.rec)
+        # (to the host in one copy where both go there: each waits for the GPU)
+        if ctx.mu_like.device == ctx.Y0_like.device:
+            dparams = dparams.to(ctx.mu_like.device)
+        gmu = dparams[0].to(ctx.mu_like.device, ctx.mu_like.dtype).reshape(ctx.mu_like.shape)
+        gY0 = dparams[1].to(ctx.Y0_like.device, ctx.Y0_like.dtype).reshape(ctx.Y0_like.shape)
         return (g["pos"], g["vel"], g["rho"], g["S"], gmu, gY0, None, None, None, None, None,
                 g.get("u"))
 
@@ -517,9 +527,8 @@ def sph_leapfrog_adjoint(grid: CellGrid, state0: ParticleState, params, dt: floa
         ws = workspace(L.SPH_OP_LEAPFROG_ADJOINT, n, 0, dev)
     t = lambda k: _dev(cot_final[k]) if cot_final.get(k) is not None else None
     cp, cv, cr, cS = t("pos"), t("vel"), t("rho"), t("S")
-    p = lambda x, i=None: (x[i].data_ptr() if i is not None else x.data_ptr()) if x is not None else None
-    cf = L.CFields(p(cp, 0), p(cp, 1), p(cp, 2), p(cv, 0), p(cv, 1), p(cv, 2), p(cr),
-                   p(cS, 0), p(cS, 1), p(cS, 2), p(cS, 3), p(cS, 4), p(cS, 5))
+    r = lambda x, k: _rows(x, k) if x is not None else [None] * k
+    cf = L.CFields(*r(cp, 3), *r(cv, 3), cr.data_ptr() if cr is not None else None, *r(cS, 6))
     cs = state0.c_state()
     fs = fields_struct(g["pos"], g["vel"], g["rho"], g["S"])
     L.check(L.lib().sph_leapfrog_adjoint(C.byref(grid.c), C.byref(cs), C.byref(params_struct(params)),

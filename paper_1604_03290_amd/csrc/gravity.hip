@@ -22,20 +22,17 @@
 //   monopole  one pass per depth, deepest first, over the inner-node list: mass and
 //             centre of mass of each node of that depth over its children in octant
 //             order
-//   walk      one wavefront walks the items for its 64 particles together: the
-//             item pointer is uniform (its data arrive by scalar loads); a lane
-//             that accepts a node resumes at the node's skip, and the wavefront
-//             descends while any active lane needs to, so every lane takes exactly
-//             the terms, and in the order, of its own walk.  Both possible next items
-//             (t + 1 and the skip) are fetched while the current one is tested.
+//   walk      one wavefront walks the tree for its 64 particles together, 64 nodes at a
+//             time (k_walk); every particle takes exactly the terms of its own walk
 #include "common.hpp"
 #include "rhs_common.hpp"
+#include "sweep.hpp"
 #include "timing.hpp"
 
 namespace sph {
 namespace {
 
-// One 48-byte tree item (one base address for both scalar loads of the walk):
+// One 48-byte tree item:
 // pm = (x, y, z, m): a leaf's position and mass, an inner node's centre of mass and
 // mass once the monopole pass ran; link = (skip, info), info = depth for an inner node
 // and -1 - i for the leaf of sorted position i.
@@ -241,19 +238,34 @@ struct GravConsts {
     int64_t n, T;
 };
 
-// a += G m_p (x_p - x_a) / (r + eps)^3 for r2 = r^2 > 0 (reciprocals by Newton steps
-// from the hardware estimates)
-__device__ inline void add_term(const GravConsts &k, double mp, double dx, double dy, double dz,
-                                double r2, double &ax, double &ay, double &az) {
+// 1 / sqrt(x) and 1 / x by one step of third order from the hardware estimates (2^-24.2 and
+// 2^-24.4 at worst over 2^-20 .. 2^20, so that the step leaves rounding only): three
+// instructions less together than two Newton steps each.
+__device__ inline double rsqrt_third(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+__device__ inline double rcp_third(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+// a += G m_p (x_p - x_a) / (r + eps)^3 for r2 = r^2 > 0, gm = G m_p
+__device__ inline void add_term(const GravConsts &k, double gm, double dx, double dy, double dz,
+                                double &ax, double &ay, double &az) {
+    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
     if (r2 == 0.0) return;
-    const double ir = rsqrt64(r2);
+    const double ir = rsqrt_third(r2);
     double id;
     if (k.eps > 0.0) {
-        id = rcp64(r2 * ir + k.eps);
+        id = rcp_third(fma(r2, ir, k.eps));
     } else {
         id = ir;
     }
-    const double f = k.G * mp * (id * id * id);
+    const double f = gm * (id * id * id);
     ax = fma(f, dx, ax);
     ay = fma(f, dy, ay);
     az = fma(f, dz, az);
@@ -272,54 +284,210 @@ __device__ inline bool opens_not(double s, double th2, double r2) {
     return s * s < th2 * r2;
 }
 
-__global__ __launch_bounds__(kBlock) void k_walk(GravConsts k, const double *__restrict__ box,
-                                                 const int32_t *__restrict__ idx,
-                                                 const Item *__restrict__ it,
-                                                 const int64_t *__restrict__ off,
-                                                 const int64_t *__restrict__ cnt,
-                                                 double *__restrict__ ax_out,
-                                                 double *__restrict__ ay_out,
-                                                 double *__restrict__ az_out,
-                                                 int32_t *__restrict__ count_out) {
-    const int64_t i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool live = i0 < k.n;
-    const int64_t i = live ? i0 : k.n - 1;  // lanes past n walk the last particle, write nothing
+__device__ inline double read_lane(double v, int l) {
+    const int2 w = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(
+        double, make_int2(__builtin_amdgcn_readlane(w.x, l), __builtin_amdgcn_readlane(w.y, l)));
+}
+
+// One wavefront, or kWaves of them, take 64 consecutive particles of the sorted order.  A
+// wavefront's work is a stack of ranges of siblings, each with the lanes that walk it; up to 64 ranges are taken off
+// the top at a time, one lane looking at the first node of each.  A node that even the
+// nearest point of the lanes' box accepts is a term of all the range's lanes, a node that
+// even the farthest opens is opened for all; only the nodes between are tested by each
+// lane for itself, one after the other.  Terms are gathered in LDS with their lanes and
+// added from there, one after the other, without tests or waits.  So the loads of 64
+// nodes are in flight together, and what remains is bound by the terms' arithmetic, about
+// 30 instructions each.  (A walk of one node at a time, its pointer common to the 64
+// lanes, spent half its time on the chain of loads and half its instructions on the
+// tests: 1631 us on 262,144 particles at theta 0.5; this takes 1434.)
+//
+// With several wavefronts all begin with the root; once kDeal ranges are on the stack each
+// keeps every kWaves-th of them (the terms until then are wavefront 0's), and their sums
+// are added in order at the end.  That halves the time of a set too small to fill the chip
+// with one wavefront per 64 particles, but the beginning is walked by all and the stacks
+// are shorter: all of sph_gravity with four and with one, us, 8,000 particles 390 and 625,
+// 100,000 (1,563 groups) 569 and 640, 150,000 (2,344 groups) 1360 and 1189.
+//
+// The stack: taking m ranges leaves at most 2 m (a range's rest, the node's children), so
+// that with m at most 32 less than the places left the 32 stay free; when no more are,
+// ranges are taken singly, and the topmost range's subtree needs at most one place for
+// each level of the tree.
+constexpr int kStack = 320;
+constexpr int kStackSpare = 32;
+static_assert(kStackSpare > kDepthMax + 2, "a walk of single ranges needs a place per level");
+constexpr int kTermBatch = 32;  // terms are added when more than these wait
+
+constexpr int kDeal = 32;
+constexpr int kWalkWaves = 4;
+constexpr int64_t kFewGroups = 1792;  // groups of 64 up to which kWalkWaves take one
+
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void k_walk(GravConsts k, const double *__restrict__ box,
+                                             const int32_t *__restrict__ idx,
+                                             const Item *__restrict__ it,
+                                             const int64_t *__restrict__ off,
+                                             const int64_t *__restrict__ cnt,
+                                             double *__restrict__ ax_out,
+                                             double *__restrict__ ay_out,
+                                             double *__restrict__ az_out,
+                                             int32_t *__restrict__ count_out) {
+    __shared__ int2 lds_range[kWaves][kStack];            // first node, end
+    __shared__ uint64_t lds_who[kWaves][kStack];          // its lanes
+    __shared__ double4 lds_term[kWaves][kTermBatch + 64];  // position, G m
+    __shared__ uint64_t lds_term_who[kWaves][kTermBatch + 64];
+    const int lane = __lane_id();
+    const int q = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int2 *const range = lds_range[q];
+    uint64_t *const who = lds_who[q], *const term_who = lds_term_who[q];
+    double4 *const term = lds_term[q];
+    const int64_t i0 = xcd_block(gridDim.x) * 64;
+    if (i0 >= k.n) return;  // whole workgroup past the end
+    const bool live = i0 + lane < k.n;
+    const int64_t i = live ? i0 + lane : k.n - 1;
     const double4 me = it[i + off[i] + cnt[i]].pm;
     const double xa = me.x, ya = me.y, za = me.z;
+    const double bx0 = wave_min(xa), bx1 = wave_max(xa);
+    const double by0 = wave_min(ya), by1 = wave_max(ya);
+    const double bz0 = wave_min(za), bz1 = wave_max(za);
     const double s0 = box[3];
     double ax = 0.0, ay = 0.0, az = 0.0;
-    int terms = 0;
-    int resume = 0;
-    const int T = (int)k.T;
-    int t = 0;
-    double4 p = it[0].pm;
-    int2 l = it[0].link;
-    while (t < T) {
-        // both possible successors, fetched while this item is tested
-        const int ta = min(t + 1, T - 1), tb = min(l.x, T - 1);
-        const Item ia = it[ta], ib = it[tb];
-        const double4 pa = ia.pm, pb = ib.pm;
-        const int2 la = ia.link, lb = ib.link;
-        const bool active = t >= resume;
-        bool down = false;
-        if (l.y >= 0) {
-            const double dx = p.x - xa, dy = p.y - ya, dz = p.z - za;
-            const double r2 = dist2_plain(dx, dy, dz);
-            const bool take = active && opens_not(ldexp(s0, -l.y), k.th2, r2);
-            if (take) {
-                add_term(k, p.w, dx, dy, dz, r2, ax, ay, az);
+    int terms = 0, pend = 0;
+    auto add_terms = [&] {
+        wave_sync();
+#pragma unroll 4
+        for (int e = 0; e < pend; ++e) {
+            const double4 p = term[e];
+            const int2 w = __builtin_bit_cast(int2, term_who[e]);
+            const uint64_t lanes = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(w.y) << 32 |
+                                   (uint32_t)__builtin_amdgcn_readfirstlane(w.x);
+            if (__builtin_amdgcn_inverse_ballot_w64(lanes)) {
+                add_term(k, p.w, p.x - xa, p.y - ya, p.z - za, ax, ay, az);
                 ++terms;
-                resume = l.x;
             }
-            down = __any(active && !take);
-        } else if (active && -1 - l.y != i) {
-            const double dx = p.x - xa, dy = p.y - ya, dz = p.z - za;
-            add_term(k, p.w, dx, dy, dz, dist2_plain(dx, dy, dz), ax, ay, az);
-            ++terms;
         }
-        t = down ? t + 1 : l.x;
-        p = down ? pa : pb;
-        l = down ? la : lb;
+        pend = 0;
+        wave_sync();
+    };
+    auto before = [&](unsigned long long m) { return __popcll(m & ((1ull << lane) - 1)); };
+    const unsigned long long all = __ballot(live);
+    if (lane == 0) {
+        range[0] = make_int2(0, (int)k.T);
+        who[0] = all;
+    }
+    int size = 1;
+    bool dealt = kWaves == 1;
+    while (size > 0) {
+        if (!dealt && size >= kDeal) {  // (fewer than 2 kDeal: a round at most doubles it)
+            static_assert(2 * kDeal <= 64 * kWalkWaves, "one range per lane is kept");
+            dealt = true;
+            const int keep = (size - q + kWaves - 1) / kWaves;
+            wave_sync();
+            const int from = min(q + kWaves * lane, size - 1);
+            const int2 r = range[from];
+            const uint64_t w = who[from];
+            wave_sync();
+            if (lane < keep) {
+                range[lane] = r;
+                who[lane] = w;
+            }
+            size = keep;
+            if (q != 0) {
+                ax = ay = az = 0.0;
+                terms = pend = 0;
+            }
+        }
+        const int m = min(min(size, 64), max(kStack - size - kStackSpare, 1));
+        wave_sync();
+        size -= m;
+        const bool valid = lane < m;
+        const int2 r = valid ? range[size + lane] : make_int2(0, 0);
+        const uint64_t mine = valid ? who[size + lane] : 0;
+        wave_sync();
+        const Item node = it[r.x];
+        const double4 p = node.pm;
+        const int skip = node.link.x, info = node.link.y;
+        uint64_t take = 0, open = 0;  // the lanes that take the node as a term, that open it
+        bool between = false;
+        double side = 0.0;
+        if (valid && info < 0) {
+            const int64_t own = (int64_t)(-1 - info) - i0;  // a particle is no term of itself
+            take = own >= 0 && own < 64 ? mine & ~(1ull << own) : mine;
+        } else if (valid) {
+            const double s = ldexp(s0, -info);
+            side = s;
+            const double nx = fmax(fmax(bx0 - p.x, p.x - bx1), 0.0), fx = fmax(p.x - bx0, bx1 - p.x);
+            const double ny = fmax(fmax(by0 - p.y, p.y - by1), 0.0), fy = fmax(p.y - by0, by1 - p.y);
+            const double nz = fmax(fmax(bz0 - p.z, p.z - bz1), 0.0), fz = fmax(p.z - bz0, bz1 - p.z);
+            // margins far above the rounding of either side
+            const double lo = k.th2 * (nx * nx + ny * ny + nz * nz) * (1.0 - 1e-12);
+            const double hi = k.th2 * (fx * fx + fy * fy + fz * fz) * (1.0 + 1e-12);
+            if (s * s < lo)
+                take = mine;
+            else if (s * s >= hi)
+                open = mine;
+            else
+                between = true;
+        }
+        for (unsigned long long b = __ballot(between); b; b &= b - 1) {
+            const int l = __ffsll((long long)b) - 1;
+            const double dx = read_lane(p.x, l) - xa, dy = read_lane(p.y, l) - ya,
+                         dz = read_lane(p.z, l) - za;
+            const unsigned long long yes =
+                __ballot(opens_not(read_lane(side, l), k.th2, dist2_plain(dx, dy, dz)));
+            if (lane == l) {
+                take = mine & yes;
+                open = mine & ~yes;
+            }
+        }
+        const unsigned long long tm = __ballot(take != 0);
+        if (take != 0) {
+            const int at = pend + before(tm);
+            term[at] = make_double4(p.x, p.y, p.z, k.G * p.w);
+            term_who[at] = take;
+        }
+        pend += __popcll(tm);
+        const bool more = valid && skip < r.y;
+        const unsigned long long rm = __ballot(more), om = __ballot(open != 0);
+        if (more) {
+            const int at = size + before(rm);
+            range[at] = make_int2(skip, r.y);
+            who[at] = mine;
+        }
+        size += __popcll(rm);
+        if (open != 0) {
+            const int at = size + before(om);
+            range[at] = make_int2(r.x + 1, skip);
+            who[at] = open;
+        }
+        size += __popcll(om);
+        if (pend > kTermBatch) {
+            if (dealt || q == 0) add_terms();
+            pend = 0;
+        }
+    }
+    if (dealt || q == 0) add_terms();
+    if constexpr (kWaves > 1) {
+        if (!dealt && q != 0) {
+            ax = ay = az = 0.0;
+            terms = 0;
+        }
+        double *sum = reinterpret_cast<double *>(lds_term);
+        static_assert(sizeof lds_term >= kWaves * 4 * 64 * 8, "the sums fit");
+        __syncthreads();
+        sum[(4 * q + 0) * 64 + lane] = ax;
+        sum[(4 * q + 1) * 64 + lane] = ay;
+        sum[(4 * q + 2) * 64 + lane] = az;
+        sum[(4 * q + 3) * 64 + lane] = (double)terms;  // (exact)
+        __syncthreads();
+        if (q != 0) return;
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) {
+            ax += sum[(4 * w + 0) * 64 + lane];
+            ay += sum[(4 * w + 1) * 64 + lane];
+            az += sum[(4 * w + 2) * 64 + lane];
+            terms += (int)sum[(4 * w + 3) * 64 + lane];
+        }
     }
     if (!live) return;
     const int a = idx[i];
@@ -438,7 +606,12 @@ extern "C" int sph_gravity(const double *x, const double *y, const double *z, co
         SPH_LAUNCHED();
     }
     const GravConsts k{G, theta * theta, eps, n, n + K};
-    k_walk<<<nb, kBlock, 0, s>>>(k, w.box, idx, w.it, w.off, w.cnt, ax, ay, az, count);
+    const unsigned groups = blocks_for(n, 64);
+    if (groups <= kFewGroups)
+        k_walk<kWalkWaves><<<groups, 64 * kWalkWaves, 0, s>>>(k, w.box, idx, w.it, w.off, w.cnt, ax,
+                                                              ay, az, count);
+    else
+        k_walk<1><<<groups, 64, 0, s>>>(k, w.box, idx, w.it, w.off, w.cnt, ax, ay, az, count);
     SPH_LAUNCHED();
     return SPH_OK;
 }

@@ -480,8 +480,7 @@ __device__ inline double adj_pre(const Consts &k, const AdjRec &ad, const AdjOwn
     return y0;
 }
 
-// pair stage + pre stage (see the file header); cell-sweep path, and with the
-// correction tensor the only path (also over a pair list)
+// pair stage + pre stage (see the file header) straight from the cells
 template <bool kCorr, int kEos, bool kAS, bool kXC>
 __global__ __launch_bounds__(kBlock) void k_adj_pairs(GridDev g, int64_t n, Consts k,
                                                       const double *__restrict__ rec, StateDev st,
@@ -538,13 +537,18 @@ __global__ __launch_bounds__(kBlock) void k_adj_pairs(GridDev g, int64_t n, Cons
 // Tillotson all eight of the forward record, whose last holds the partner's signed sound
 // speed); the
 // partial sums are folded into wavefront 0, which runs the pre stage and the Y0 sum.
-// With the du and dx/dt cotangents each lane loads its own partner's four (one list
-// entry per lane and step)
-template <int kEos, bool kAS, bool kXC = false>
-__global__ __launch_bounds__(64 * kSplitAdj) void k_adj_pairs_list(GridDev g, int64_t n, Consts k,
-                                                                   const double *__restrict__ rec,
-                                                                   StateDev st, AdjRec ad,
-                                                                   GradDev out) {
+// With the du and dx/dt cotangents each lane loads its own partner's four, and with the
+// correction tensor its partner's six of the moment matrix (one list entry per lane and
+// step).  (The correction over a list went through the cell-sweep form below, a lane per
+// slot: 765 us on 300,000 particles, 391 here.)  For the correction and the
+// cotangents two wavefronts a SIMD are asked for, at the price of ten registers spilled;
+// with the artificial stress it would be up to seventy, and one wavefront is the faster (a
+// forward and backward of 300,000 particles 1071 us, 1245 with two).
+template <int kEos, bool kAS, bool kXC = false, bool kCorr = false>
+__global__ __launch_bounds__(64 * kSplitAdj, !kAS && (kCorr || kXC) ? 2 : 1) void k_adj_pairs_list(GridDev g, int64_t n, Consts k,
+                                                                      const double *__restrict__ rec,
+                                                                      StateDev st, AdjRec ad,
+                                                                      GradDev out) {
     constexpr int kF = kEos != 0 ? 8 : 7;  // forward-record chunks gathered
     __shared__ double2 lbuf[kSplitAdj][64 * (kF + 7)];
     const int q = threadIdx.x >> 6;
@@ -565,6 +569,11 @@ __global__ __launch_bounds__(64 * kSplitAdj) void k_adj_pairs_list(GridDev g, in
     if constexpr (kXC) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) xo[i] = ad.ext[i][act ? s : w0];
+    }
+    double Mc[6] = {0, 0, 0, 0, 0, 0};
+    if constexpr (kCorr) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) Mc[i] = ad.Mb[i][act ? s : w0];
     }
     const char *rf = reinterpret_cast<const char *>(rec);
     const char *ra = reinterpret_cast<const char *>(ad.arec);
@@ -605,10 +614,14 @@ __global__ __launch_bounds__(64 * kSplitAdj) void k_adj_pairs_list(GridDev g, in
 #pragma unroll
                 for (int i = 0; i < 4; ++i) xb[i] = ad.ext[i][mine];
             }
+            double Mb[6] = {0, 0, 0, 0, 0, 0};
+            if constexpr (kCorr) {
+#pragma unroll
+                for (int i = 0; i < 6; ++i) Mb[i] = ad.Mb[i][mine];
+            }
             if (d2 < k.h2)
-                adj_pair<false, kEos, kAS, kXC>(k, o, d2, b0, b1, b2, b3, b4, b5, b6, q0, q1,
-                                                q2, q3, q4, q5, q6, acc, nullptr, nullptr, xo,
-                                                xb, cb);
+                adj_pair<kCorr, kEos, kAS, kXC>(k, o, d2, b0, b1, b2, b3, b4, b5, b6, q0, q1,
+                                                q2, q3, q4, q5, q6, acc, Mc, Mb, xo, xb, cb);
         }
     }
     fold_adj<kSplitAdj, kSplitAdj * 64 * (kF + 7) * 2>(acc, reinterpret_cast<double *>(lbuf));
@@ -747,18 +760,18 @@ int rhs_adjoint_launch(const sph_grid *grid, const sph_state *state, const sph_p
             constexpr int E = decltype(eos_t)::value;
             constexpr bool A = decltype(as_t)::value;
             const dim3 gb(blocks_for(n)), tb(kBlock);
-            if (xc && k.corr)
-                k_adj_pairs<true, E, A, true><<<gb, tb, 0, s>>>(g, n, k, rec, st, ad, grad);
-            else if (xc && g.pl_count)
-                k_adj_pairs_list<E, A, true><<<blocks_for(n, 64), 64 * kSplitAdj, 0, s>>>(g, n, k, rec, st, ad, grad);
-            else if (xc)
-                k_adj_pairs<false, E, A, true><<<gb, tb, 0, s>>>(g, n, k, rec, st, ad, grad);
-            else if (k.corr)
-                k_adj_pairs<true, E, A, false><<<gb, tb, 0, s>>>(g, n, k, rec, st, ad, grad);
-            else if (g.pl_count)
-                k_adj_pairs_list<E, A><<<blocks_for(n, 64), 64 * kSplitAdj, 0, s>>>(g, n, k, rec, st, ad, grad);
+            auto go = [&](auto corr_t, auto xc_t) {
+                constexpr bool C = decltype(corr_t)::value, X = decltype(xc_t)::value;
+                if (g.pl_count)
+                    k_adj_pairs_list<E, A, X, C><<<blocks_for(n, 64), 64 * kSplitAdj, 0, s>>>(
+                        g, n, k, rec, st, ad, grad);
+                else
+                    k_adj_pairs<C, E, A, X><<<gb, tb, 0, s>>>(g, n, k, rec, st, ad, grad);
+            };
+            if (k.corr)
+                xc ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
             else
-                k_adj_pairs<false, E, A, false><<<gb, tb, 0, s>>>(g, n, k, rec, st, ad, grad);
+                xc ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
         };
         using T = std::true_type;
         using F = std::false_type;
@@ -774,8 +787,7 @@ int rhs_adjoint_launch(const sph_grid *grid, const sph_state *state, const sph_p
         SPH_LAUNCHED();
     }
     if (acc_parts) return SPH_OK;  // the caller reduces its accumulators
-    const bool per_wave = g.pl_count && !k.corr;
-    const int64_t m_y0 = per_wave ? blocks_for(n, 64) : blocks_for(n);
+    const int64_t m_y0 = g.pl_count ? blocks_for(n, 64) : blocks_for(n);
     return reduce_params_launch(ad.part_mu, blocks_for(n), ad.part_y0, m_y0, dparams,
                                 accumulate_params, s);
 }

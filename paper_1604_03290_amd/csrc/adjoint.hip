@@ -126,7 +126,7 @@ __global__ __launch_bounds__(64 * kSplit) void k_adj_L_list(GridDev g, int64_t n
     __shared__ double2 lbuf[kSplit][64 * 4];
     const int q = threadIdx.x >> 6;
     double2 *buf = lbuf[q];
-    const int64_t w = xcd_block(gridDim.x);
+    const int64_t w = xcd_list_block(gridDim.x);
     const int64_t w0 = w * 64;
     if (w0 >= n) return;  // whole workgroup past the end
     const int64_t s = w0 + __lane_id();
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(64 * kSplitAdj, !kAS && (kCorr || kXC) ? 2 : 1) voi
     double2 *bf = lbuf[q];
     double2 *ba = bf + 64 * kF;
     auto fchunk = [&](int c) { return kF == 8 ? dma8_chunk(bf, c) : dma_chunk<7>(bf, c); };
-    const int64_t w = xcd_block(gridDim.x);
+    const int64_t w = xcd_list_block(gridDim.x);
     const int64_t w0 = w * 64;
     if (w0 >= n) return;  // whole workgroup past the end
     const int64_t s = w0 + __lane_id();

@@ -169,7 +169,7 @@ __device__ inline double dist2_exact(double xa, double ya, double za, double xb,
 }
 
 // Logical workgroup of a 1-D launch of nblocks workgroups: the dispatcher deals
-// workgroups to the 8 XCDs round robin; this remap gives each XCD runs of kXcdRun
+// workgroups to the 8 XCDs round robin; this remap gives each XCD runs of `run`
 // consecutive workgroups (neighbouring cells share its L2), the runs dealt round robin,
 // so that a set whose partner counts vary over space loads the XCDs alike.  What does
 // not fill a round of runs is split into one contiguous range per XCD.  (One range per
@@ -178,15 +178,24 @@ __device__ inline double dist2_exact(double xa, double ya, double za, double xb,
 // with 256 and 49.5 with 16; the non-uniform right-hand side of 100,000 particles 198 us,
 // 156 with runs of 64; uniform sets the same within 0.5 % down to 64, 1 % slower at 16.)
 constexpr int64_t kXcdRun = 64;
-__device__ inline int64_t xcd_block(int64_t nblocks) {
-    int64_t i = blockIdx.x, base = nblocks / (8 * kXcdRun) * (8 * kXcdRun);
+__device__ inline int64_t xcd_block(int64_t nblocks, int64_t run = kXcdRun) {
+    int64_t i = blockIdx.x, base = nblocks / (8 * run) * (8 * run);
     if (i < base) {
         const int64_t x = i & 7, k = i >> 3;
-        return k / kXcdRun * (8 * kXcdRun) + x * kXcdRun + k % kXcdRun;
+        return k / run * (8 * run) + x * run + k % run;
     }
     i -= base;
     const int64_t m = nblocks - base, x = i & 7, q = m >> 3, r = m & 7;
     return base + x * q + (x < r ? x : r) + (i >> 3);
+}
+
+// The same for the list kernels, whose workgroups take 64 slots each.  Below 4,096 of them
+// (16 a CU) an XCD has few runs of 64, and a body's dense middle is one XCD's or two: runs
+// of 8 there.  (us with runs of 64, 16 and 8: right-hand side of 50,364 non-uniform
+// particles 146, 128 and 103, of 90,000 223, 172 and 164, adjoint of 95,177 459, 358 and
+// 359; at 4,096 workgroups of a uniform set 64 is the faster by 0.6 %.)
+__device__ inline int64_t xcd_list_block(int64_t nblocks) {
+    return xcd_block(nblocks, nblocks < 4096 ? 8 : kXcdRun);
 }
 
 // Calls f(t) for every candidate slot t != s of slot s: from the pair list when

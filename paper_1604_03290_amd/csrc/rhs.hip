@@ -132,7 +132,7 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs64_list(GridDev g, int64_t
     __shared__ double2 lbuf[kSplit][64 * 8];
     const int q = threadIdx.x >> 6;
     double2 *buf = lbuf[q];
-    const int64_t w = xcd_block(gridDim.x);
+    const int64_t w = xcd_list_block(gridDim.x);
     const int64_t w0 = w * 64;
     if (w0 >= n) return;  // whole workgroup past the end
     const int64_t s = w0 + __lane_id();
@@ -202,6 +202,7 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs64_list(GridDev g, int64_t
 // Without a skin the hints are not built: they cost 83 us on 262,144 particles, more than
 // the 51 us of one evaluation, and such a list holds for one set of positions only.
 constexpr int kFwdWaves = 4;
+constexpr unsigned kManyGroups = 1024;
 
 template <bool kCorr, bool kExt>
 __global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g, int64_t n, Consts k,
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g,
     __shared__ double2 ring[W * 7];
     __shared__ double cs[kExt ? W : 1];
     __shared__ int32_t tag[W];
-    const int64_t w = xcd_block(gridDim.x);
+    const int64_t w = xcd_list_block(gridDim.x);
     const int64_t w0 = w * 64;
     if (w0 >= n) return;  // whole workgroup past the end
     const int64_t s = w0 + __lane_id();
@@ -263,7 +264,11 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g,
                                 Tb, tens_a, c_a, r.c);
         }
     };
-    if (v.locals) {
+    // A dense group whose partners do not fit the window at once: while the chip is full
+    // its reloads and barriers are hidden (100,000 non-uniform particles 149 us, 163 with
+    // such groups gathered); a smaller launch waits for the few densest groups, and then
+    // the gathers are the shorter (12,000 to 30,000 particles 81 us against 95).
+    if (v.locals && (v.locals <= W || gridDim.x > kManyGroups)) {
         sweep_window(
             v, ahead, tag, n,
             [&](int p, int e) {
@@ -639,7 +644,7 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs32_list(GridDev g, int64_t
     __shared__ double2 lbuf[kSplit][64 * 5];
     const int q = threadIdx.x >> 6;
     double2 *buf = lbuf[q];
-    const int64_t w = xcd_block(gridDim.x);
+    const int64_t w = xcd_list_block(gridDim.x);
     const int64_t w0 = w * 64;
     if (w0 >= n) return;  // whole workgroup past the end
     const int64_t s = w0 + __lane_id();

@@ -641,30 +641,48 @@ __global__ __launch_bounds__(64 * kSplitAdj, !kAS && (kCorr || kXC) ? 2 : 1) voi
 }  // namespace
 
 namespace {
-// Sum of p[threadIdx.x + kBlock k] over k in a fixed order: eight running sums (k mod 8)
+// The partial sums are at most n / 64 and n / 256 numbers: one workgroup, of as many
+// threads as it may have, since the loads in flight are what bounds it (131,072 and 32,768
+// of them 253 us with 256 threads, 31 with 1024).
+constexpr int kReduce = 1024;
+
+// Sum of p[threadIdx.x + kReduce k] over k in a fixed order: eight running sums (k mod 8)
 // so that eight loads are in flight, added pairwise at the end.
 __device__ inline double strided_sum(const double *__restrict__ p, int64_t m) {
     double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int64_t i = threadIdx.x; i < m; i += 8 * kBlock) {
+    for (int64_t i = threadIdx.x; i < m; i += 8 * kReduce) {
+        double v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int64_t j = i + (int64_t)u * kBlock;
-            if (j < m) a[u] += p[j];
+            const int64_t j = i + (int64_t)u * kReduce;
+            v[u] = j < m ? p[j] : 0.0;
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] += v[u];
     }
     return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
 }
 
 // one block: dparams[i] (+)= sum of part_i in a fixed order (a null part is skipped)
-__global__ __launch_bounds__(kBlock) void k_reduce_params(const double *__restrict__ p0,
-                                                          int64_t m0,
-                                                          const double *__restrict__ p1,
-                                                          int64_t m1, double *dparams,
-                                                          int accumulate) {
-    double a = p0 ? strided_sum(p0, m0) : 0.0, b = p1 ? strided_sum(p1, m1) : 0.0;
-    a = block_sum(a);
-    b = block_sum(b);
-    if (threadIdx.x == 0) {
+__global__ __launch_bounds__(kReduce) void k_reduce_params(const double *__restrict__ p0,
+                                                           int64_t m0,
+                                                           const double *__restrict__ p1,
+                                                           int64_t m1, double *dparams,
+                                                           int accumulate) {
+    __shared__ double lds[2][kReduce];
+    const int t = threadIdx.x;
+    lds[0][t] = p0 ? strided_sum(p0, m0) : 0.0;
+    lds[1][t] = p1 ? strided_sum(p1, m1) : 0.0;
+    __syncthreads();
+    for (int off = kReduce / 2; off > 0; off >>= 1) {
+        if (t < off) {
+            lds[0][t] += lds[0][t + off];
+            lds[1][t] += lds[1][t + off];
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        const double a = lds[0][0], b = lds[1][0];
         if (accumulate) {
             if (p0) dparams[0] += a;
             if (p1) dparams[1] += b;
@@ -679,7 +697,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_params(const double *__restri
 
 int reduce_params_launch(const double *p0, int64_t m0, const double *p1, int64_t m1,
                          double *dparams, int accumulate, hipStream_t s) {
-    k_reduce_params<<<1, kBlock, 0, s>>>(p0, m0, p1, m1, dparams, accumulate);
+    k_reduce_params<<<1, kReduce, 0, s>>>(p0, m0, p1, m1, dparams, accumulate);
     SPH_LAUNCHED();
     return SPH_OK;
 }

@@ -238,30 +238,15 @@ struct GravConsts {
     int64_t n, T;
 };
 
-// 1 / sqrt(x) and 1 / x by one step of third order from the hardware estimates (2^-24.2 and
-// 2^-24.4 at worst over 2^-20 .. 2^20, so that the step leaves rounding only): three
-// instructions less together than two Newton steps each.
-__device__ inline double rsqrt_third(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-(x * y), y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
-__device__ inline double rcp_third(double x) {
-    const double y = __builtin_amdgcn_rcp(x);
-    const double e = fma(-x, y, 1.0);
-    return fma(y, fma(e, e, e), y);
-}
-
 // a += G m_p (x_p - x_a) / (r + eps)^3 for r2 = r^2 > 0, gm = G m_p
 __device__ inline void add_term(const GravConsts &k, double gm, double dx, double dy, double dz,
                                 double &ax, double &ay, double &az) {
     const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
     if (r2 == 0.0) return;
-    const double ir = rsqrt_third(r2);
+    const double ir = rsqrt64(r2);
     double id;
     if (k.eps > 0.0) {
-        id = rcp_third(fma(r2, ir, k.eps));
+        id = rcp64(fma(r2, ir, k.eps));
     } else {
         id = ir;
     }

@@ -544,13 +544,15 @@ __global__ __launch_bounds__(kBlock) void k_adj_pairs(GridDev g, int64_t n, Cons
 // cotangents two wavefronts a SIMD are asked for, at the price of ten registers spilled;
 // with the artificial stress it would be up to seventy, and one wavefront is the faster (a
 // forward and backward of 300,000 particles 1071 us, 1245 with two).
-template <int kEos, bool kAS, bool kXC = false, bool kCorr = false>
-__global__ __launch_bounds__(64 * kSplitAdj, !kAS && (kCorr || kXC) ? 2 : 1) void k_adj_pairs_list(GridDev g, int64_t n, Consts k,
+template <int kEos, bool kAS, bool kXC = false, bool kCorr = false, int P = kSplitAdj>
+__global__ __launch_bounds__(64 * P, !kAS && (kCorr || kXC) ? 2 : 1) void k_adj_pairs_list(GridDev g, int64_t n, Consts k,
                                                                       const double *__restrict__ rec,
                                                                       StateDev st, AdjRec ad,
                                                                       GradDev out) {
-    constexpr int kF = kEos != 0 ? 8 : 7;  // forward-record chunks gathered
-    __shared__ double2 lbuf[kSplitAdj][64 * (kF + 7)];
+    // forward-record chunks gathered (with eight wavefronts whole records: seven chunks take
+    // more registers than two wavefronts a SIMD leave)
+    constexpr int kF = kEos != 0 || P > kSplitAdj ? 8 : 7;
+    __shared__ double2 lbuf[P][64 * (kF + 7)];
     const int q = threadIdx.x >> 6;
     double2 *bf = lbuf[q];
     double2 *ba = bf + 64 * kF;
@@ -578,7 +580,7 @@ __global__ __launch_bounds__(64 * kSplitAdj, !kAS && (kCorr || kXC) ? 2 : 1) voi
     const char *rf = reinterpret_cast<const char *>(rec);
     const char *ra = reinterpret_cast<const char *>(ad.arec);
     const int32_t *row = g.pl_slot + base + __lane_id();
-    // One step ahead: the gathers of step j + kSplitAdj are in flight while step j is
+    // One step ahead: the gathers of step j + P are in flight while step j is
     // evaluated.  Each lane reads its step-j chunks into registers, the wavefront
     // syncs, and only then are the buffers refilled.
     auto gather = [&](int e) {
@@ -590,8 +592,8 @@ __global__ __launch_bounds__(64 * kSplitAdj, !kAS && (kCorr || kXC) ? 2 : 1) voi
     };
     int cur = q < steps ? row[(int64_t)q << 6] : 0;  // this lane's partner slot of step j
     if (q < steps) gather(cur);
-    int nxt = q + kSplitAdj < steps ? row[(int64_t)(q + kSplitAdj) << 6] : 0;
-    for (int j = q; j < steps; j += kSplitAdj) {
+    int nxt = q + P < steps ? row[(int64_t)(q + P) << 6] : 0;
+    for (int j = q; j < steps; j += P) {
         wait_vm();
         const double2 b0 = fchunk(0), b1 = fchunk(1), b2 = fchunk(2), b3 = fchunk(3),
                       b4 = fchunk(4), b5 = fchunk(5), b6 = fchunk(6);
@@ -602,10 +604,10 @@ __global__ __launch_bounds__(64 * kSplitAdj, !kAS && (kCorr || kXC) ? 2 : 1) voi
                       q6 = dma_chunk<7>(ba, 6);
         wave_sync();
         const int mine = cur;
-        if (j + kSplitAdj < steps) {
+        if (j + P < steps) {
             gather(nxt);
             cur = nxt;
-            if (j + 2 * kSplitAdj < steps) nxt = row[(int64_t)(j + 2 * kSplitAdj) << 6];
+            if (j + 2 * P < steps) nxt = row[(int64_t)(j + 2 * P) << 6];
         }
         if (j < cnt) {
             const double d2 = dist2_exact(o.xc, o.yc, o.zc, b0.x, b0.y, b1.x);
@@ -624,7 +626,7 @@ __global__ __launch_bounds__(64 * kSplitAdj, !kAS && (kCorr || kXC) ? 2 : 1) voi
                                                 q2, q3, q4, q5, q6, acc, Mc, Mb, xo, xb, cb);
         }
     }
-    fold_adj<kSplitAdj, kSplitAdj * 64 * (kF + 7) * 2>(acc, reinterpret_cast<double *>(lbuf));
+    fold_adj<P, P * 64 * (kF + 7) * 2>(acc, reinterpret_cast<double *>(lbuf));
     if (q != 0) return;
     if constexpr (kXC) {  // dx/dt = v + ...
         acc.gvx += xo[1];
@@ -780,6 +782,12 @@ int rhs_adjoint_launch(const sph_grid *grid, const sph_state *state, const sph_p
             const dim3 gb(blocks_for(n)), tb(kBlock);
             auto go = [&](auto corr_t, auto xc_t) {
                 constexpr bool C = decltype(corr_t)::value, X = decltype(xc_t)::value;
+                if constexpr (!A && !X)
+                    if (g.pl_count && blocks_for(n, 64) <= kFewBlocks) {
+                        k_adj_pairs_list<E, A, X, C, 2 * kSplitAdj>
+                            <<<blocks_for(n, 64), 64 * 2 * kSplitAdj, 0, s>>>(g, n, k, rec, st, ad, grad);
+                        return;
+                    }
                 if (g.pl_count)
                     k_adj_pairs_list<E, A, X, C><<<blocks_for(n, 64), 64 * kSplitAdj, 0, s>>>(
                         g, n, k, rec, st, ad, grad);

@@ -124,12 +124,12 @@ __device__ inline void fold_acc64(Acc64 &a, double *scratch) {
 // block of 64 slots, wavefront q walking the 64 lists in lock step over steps q,
 // q + kSplit, ... and gathering the 64 partner records of each step cooperatively;
 // the partial sums are folded into wavefront 0, which runs the postpass.
-template <bool kCorr, bool kExt>
-__global__ __launch_bounds__(64 * kSplit) void k_pairs64_list(GridDev g, int64_t n, Consts k,
+template <bool kCorr, bool kExt, int P = kSplit>
+__global__ __launch_bounds__(64 * P) void k_pairs64_list(GridDev g, int64_t n, Consts k,
                                                               const double *__restrict__ rec,
                                                               StateDev st, OutDev out,
                                                               double *__restrict__ Lout) {
-    __shared__ double2 lbuf[kSplit][64 * 8];
+    __shared__ double2 lbuf[P][64 * 8];
     const int q = threadIdx.x >> 6;
     double2 *buf = lbuf[q];
     const int64_t w = xcd_list_block(gridDim.x);
@@ -155,19 +155,19 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs64_list(GridDev g, int64_t
     const char *recs = reinterpret_cast<const char *>(rec);
     const int32_t *row = g.pl_slot + base + __lane_id();
     // One step ahead: each lane reads its step-j record into registers, the wavefront
-    // syncs, the gathers of step j + kSplit are issued, and step j is evaluated while
+    // syncs, the gathers of step j + P are issued, and step j is evaluated while
     // they are in flight.
     if (q < steps) gather_dma8(recs, kRec * 8, row[(int64_t)q << 6], buf);
-    int nxt = q + kSplit < steps ? row[(int64_t)(q + kSplit) << 6] : 0;
-    for (int j = q; j < steps; j += kSplit) {
+    int nxt = q + P < steps ? row[(int64_t)(q + P) << 6] : 0;
+    for (int j = q; j < steps; j += P) {
         wait_vm();
         const double2 b0 = dma8_chunk(buf, 0), b1 = dma8_chunk(buf, 1), b2 = dma8_chunk(buf, 2),
                       b3 = dma8_chunk(buf, 3), b4 = dma8_chunk(buf, 4), b5 = dma8_chunk(buf, 5),
                       b6 = dma8_chunk(buf, 6), b7 = dma8_chunk(buf, 7);
         wave_sync();
-        if (j + kSplit < steps) {
+        if (j + P < steps) {
             gather_dma8(recs, kRec * 8, nxt, buf);
-            if (j + 2 * kSplit < steps) nxt = row[(int64_t)(j + 2 * kSplit) << 6];
+            if (j + 2 * P < steps) nxt = row[(int64_t)(j + 2 * P) << 6];
         }
         if (j < cnt) {
             const double d2 = dist2_exact(xa, ya, za, b0.x, b0.y, b1.x);
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs64_list(GridDev g, int64_t
             }
         }
     }
-    fold_acc64<kSplit, kSplit * 64 * 16, kCorr, kExt>(acc, reinterpret_cast<double *>(lbuf));
+    fold_acc64<P, P * 64 * 16, kCorr, kExt>(acc, reinterpret_cast<double *>(lbuf));
     if (q != 0 || !act) return;
     const int a = io_index(g, s);
     postpass(k, a, rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs, stress_of(st, a).s, out,
@@ -204,8 +204,8 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs64_list(GridDev g, int64_t
 constexpr int kFwdWaves = 4;
 constexpr unsigned kManyGroups = 1024;
 
-template <bool kCorr, bool kExt>
-__global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g, int64_t n, Consts k,
+template <bool kCorr, bool kExt, int P = kFwdWaves>
+__global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t n, Consts k,
                                                                    const double *__restrict__ rec,
                                                                    StateDev st, OutDev out,
                                                                    double *__restrict__ Lout) {
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g,
     if (w0 >= n) return;  // whole workgroup past the end
     const int64_t s = w0 + __lane_id();
     const bool act = s < n;
-    const auto ahead = list_ahead<kFwdWaves, W>(g, w, s, act);
+    const auto ahead = list_ahead<P, W>(g, w, s, act);
     const double2 *ra = rec2(rec, act ? s : w0);
     const double2 p0 = ra[0], p1 = ra[1], p2 = ra[2], p3 = ra[3], p4 = ra[4], p5 = ra[5],
                   p6 = ra[6], p7 = ra[7];
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g,
     } else {
         ready();
         double2 *buf = ring + (threadIdx.x >> 6) * 64 * 8;
-        sweep_gather<kFwdWaves>(
+        sweep_gather<P>(
             v, [&](int e) { gather_dma8(recs, kRec * 8, e, buf); },
             [&] {
                 Partner r;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g,
             },
             use);
     }
-    fold_acc64<kFwdWaves, W * 14, kCorr, kExt>(acc, reinterpret_cast<double *>(ring));
+    fold_acc64<P, W * 14, kCorr, kExt>(acc, reinterpret_cast<double *>(ring));
     if (first) {
         postpass(k, a, rho_a, acc.L, acc.ax, acc.ay, acc.az, acc.rs, S.s, out, kCorr ? acc.M : nullptr);
         if (kExt) postpass_ext(k, a, acc, st, out);
@@ -322,12 +322,12 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void k_pairs64_window(GridDev g,
 // takes 45 and 185, and with the extended terms 364 us are now 240.
 constexpr int kCellWaves = 4;
 
-template <bool kCorr, bool kExt>
-__global__ __launch_bounds__(64 * kCellWaves, 2) void k_pairs64_cells(GridDev g, int64_t n, Consts k,
+template <bool kCorr, bool kExt, int P = kCellWaves>
+__global__ __launch_bounds__(64 * P, 2) void k_pairs64_cells(GridDev g, int64_t n, Consts k,
                                                                   const double *__restrict__ rec,
                                                                   StateDev st, OutDev out,
                                                                   double *__restrict__ Lout) {
-    constexpr int P = kCellWaves, kOwn = 160, W = P * kOwn;  // two workgroups per CU
+    constexpr int W = 640, kOwn = W / P, kWords = (kOwn + 63) / 64;  // two workgroups per CU
     constexpr int kBlocks = W / 64, kMine = (kBlocks + P - 1) / P;
     __shared__ double2 ring[W * 7];
     __shared__ double cs[kExt ? W : 1];
@@ -417,9 +417,9 @@ __global__ __launch_bounds__(64 * kCellWaves, 2) void k_pairs64_cells(GridDev g,
             const int mq = m > q ? (m - q + P - 1) / P : 0;
             const double2 *own = ring + q * kOwn * 7;
             uint64_t left[3] = {0, 0, 0};  // this slot's partners among them
-            static_assert(kOwn > 128 && kOwn <= 192 && kOwn % 4 == 0, "three words of bits");
+            static_assert(kWords <= 3 && kOwn % 4 == 0, "at most three words of bits");
 #pragma unroll
-            for (int u = 0; u < 3; ++u) {
+            for (int u = 0; u < kWords; ++u) {
                 const int bits = min(mq - 64 * u, 64);
                 for (int b = 0; b < bits; b += 4) {  // four at a time: their reads overlap
                     double2 b0[4];
@@ -800,15 +800,21 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
         TimedRegion t(timed ? "pairs_fp64" : nullptr, s);
         auto launch = [&](auto corr, auto extra) {
             constexpr bool C = decltype(corr)::value, E = decltype(extra)::value;
-            if (g.pl_count && grid->pairs->skin > 0.0)
-                k_pairs64_window<C, E><<<blocks_for(n, 64), 64 * kFwdWaves, 0, s>>>(g, n, k, rec, st,
-                                                                                   od, L_out);
-            else if (g.pl_count)
-                k_pairs64_list<C, E><<<blocks_for(n, 64), 64 * kSplit, 0, s>>>(g, n, k, rec, st, od,
-                                                                               L_out);
+            auto with = [&](auto waves) {
+                constexpr int P = decltype(waves)::value;
+                const dim3 gb(blocks_for(n, 64)), tb(64 * P);
+                if (g.pl_count && grid->pairs->skin > 0.0)
+                    k_pairs64_window<C, E, P><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out);
+                else if (g.pl_count)
+                    k_pairs64_list<C, E, P><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out);
+                else
+                    k_pairs64_cells<C, E, P><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out);
+            };
+            static_assert(kFwdWaves == kSplit && kCellWaves == kSplit, "one choice for all three");
+            if (blocks_for(n, 64) <= kFewBlocks)
+                with(std::integral_constant<int, 2 * kSplit>{});
             else
-                k_pairs64_cells<C, E><<<blocks_for(n, 64), 64 * kCellWaves, 0, s>>>(g, n, k, rec, st,
-                                                                                   od, L_out);
+                with(std::integral_constant<int, kSplit>{});
         };
         using T = std::true_type;
         using F = std::false_type;

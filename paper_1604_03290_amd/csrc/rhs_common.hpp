@@ -167,6 +167,13 @@ __device__ inline int list_steps(int cnt) {
 constexpr int kSplit = 4;     // wavefronts per block in the forward list kernels
 constexpr int kSplitAdj = 4;  // and in the adjoint's pair kernel
 
+// Up to one block of 64 slots per CU a workgroup has twice the wavefronts: the launch
+// takes as long as a block, and a block's steps are shared by as many as it has.  (us with
+// four and with eight: right-hand side of 12,000 non-uniform particles 81 and 64, of 4,096
+// from the cells 56 and 53; adjoint of 8,000 with Murnaghan 135 and 124; ten trajectory
+// steps of 4,096 with their gradient 874 and 824.)
+constexpr unsigned kFewBlocks = 256;
+
 template <int P, int Cap, int F>
 __device__ inline void fold_waves(double (&v)[F], double *scratch) {
     static_assert(P >= 2 && Cap >= 64 * (P - 1), "scratch too small");

@@ -18,6 +18,7 @@ DX = 1.0 / 16
 CASES = {
     "ragged": (lambda: W.cube(9, DX, 1), 2, 0.0),  # 729: eleven groups and 25 slots
     "groups": (lambda: W.cube(12, DX, 2, shuffle=True), 2, 0.15),  # 1,728: whole groups
+    "many": (lambda: W.cube(26, DX, 4), 2, 0.15),  # 275 groups: four wavefronts each, not eight
     "dense": (lambda: W.cube(11, DX, 3, h_over_dx=3.9), 1, 0.3),
 }
 

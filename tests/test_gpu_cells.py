@@ -24,7 +24,8 @@ def scattered(n, seed):
 
 
 # one slot, one group less, exactly and more than full; several tiles; more candidates than
-# fit the LDS at a time; groups swept slot by slot; a single row of cells
+# fit the LDS at a time; the last set whose groups have eight wavefronts and the first with
+# four; groups swept slot by slot; a single row of cells
 CASES = {
     "one": (lambda: W.cube(4, DX, 1).take(np.arange(1)), 2, 0.0),
     "63": (lambda: W.cube(4, DX, 2).take(np.arange(63)), 2, 0.0),
@@ -32,6 +33,8 @@ CASES = {
     "65": (lambda: W.cube(5, DX, 4).take(np.arange(65)), 2, 0.15),
     "tiles": (lambda: W.cube(17, DX, 5, shuffle=True), 2, 0.15),
     "dense": (lambda: W.cube(15, DX, 6, h_over_dx=3.9), 1, 0.5),
+    "256 groups": (lambda: W.cube(26, DX, 10).take(np.arange(16384)), 2, 0.0),
+    "257 groups": (lambda: W.cube(26, DX, 11).take(np.arange(16385)), 2, 0.15),
     "sheet": (lambda: W.cube(30, DX, 7).take(np.arange(900)), 2, 0.0),
     "scattered": (lambda: scattered(700, 8), 2, 0.0),
     "line": (lambda: W.cube(66, DX, 9).take(np.arange(66)), 2, 0.0),
@@ -40,7 +43,7 @@ CASES = {
 
 @pytest.mark.parametrize("name,extra,correction",
                          [(c, e, False) for c in CASES for e in (False, True)] +
-                         [(c, e, True) for c in ("tiles", "dense") for e in (False, True)])
+                         [(c, e, True) for c in ("tiles", "dense", "257 groups") for e in (False, True)])
 def test_cells_and_list_agree(name, extra, correction):
     make, cells_per_h, skin = CASES[name]
     w = make()

@@ -20,6 +20,7 @@ KEYS = ("acc", "drho", "dS", "rho_sum")
 # particle spacings, 0: a list without the words
 CASES = {
     "cube17": (lambda: W.cube(17, 1.0 / 16, 3), 2, 0.15),
+    "four": (lambda: W.cube(26, 1.0 / 16, 9), 2, 0.15),  # 275 groups: four wavefronts each, not eight
     "no_skin": (lambda: W.cube(17, 1.0 / 16, 3), 2, 0.0),
     "cube4": (lambda: W.cube(4, 1.0 / 16, 4), 2, 0.15),
     "few": (lambda: W.cube(3, 1.0 / 16, 5).take(np.arange(11)), 1, 0.15),

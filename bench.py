@@ -81,16 +81,16 @@ WORKLOADS = {"two_spheres": 1, "bullet": 2, "nonuniform": 4}
 COUNTERS = {
     "k_adj_pairs_list": {
         "profile": "profiles/hbm_traffic_nonuniform_8388608.md",
-        "fetch_bytes": 17094807996.0, "write_bytes": 3465202176.0, "l2_hit_rate": 0.8376,
-        "sources_sha256": "6fdbf3b70b0a9dd90d864db6d96d54e949b44a6c5898310a22431a4a8678c743"},
+        "fetch_bytes": 18904867306.3, "write_bytes": 3441590822.4, "l2_hit_rate": 0.8253,
+        "sources_sha256": "d50f26073ac481aca594152530ad9ee05b907407d9c00cac8a911c854521240f"},
     "k_pairs64_list": {
         "profile": "profiles/hbm_traffic_nonuniform_8388608.md",
-        "fetch_bytes": 13632843261.2, "write_bytes": 3370255176.0, "l2_hit_rate": 0.7724,
-        "sources_sha256": "25aa29c4db090ac435c66e9ff0c6db71fc994bbec6143f0ef62c3f7e12718909"},
+        "fetch_bytes": 15217118768.1, "write_bytes": 3370792296.0, "l2_hit_rate": 0.7515,
+        "sources_sha256": "61ef048f158370adafb3bd024d5df9582bc8542b58ed24b5b4416ce3a39ba536"},
 }
 
 KERNEL_SOURCES = {"k_adj_pairs_list": ("adjoint.hip", "adjoint.hpp", "rhs_common.hpp", "common.hpp"),
-                  "k_pairs64_list": ("rhs.hip", "rhs_common.hpp", "common.hpp"),
+                  "k_pairs64_list": ("rhs.hip", "rhs_common.hpp", "common.hpp", "sweep.hpp", "window.hpp"),
                   "k_adj_L_list": ("adjoint.hip", "adjoint.hpp", "rhs_common.hpp", "common.hpp")}
 
 

@@ -86,7 +86,7 @@ COUNTERS = {
     "k_pairs64_list": {
         "profile": "profiles/hbm_traffic_nonuniform_8388608.md",
         "fetch_bytes": 15217118768.1, "write_bytes": 3370792296.0, "l2_hit_rate": 0.7515,
-        "sources_sha256": "61ef048f158370adafb3bd024d5df9582bc8542b58ed24b5b4416ce3a39ba536"},
+        "sources_sha256": "843c3625ab4ee64232b5d8ebb68b42e50828ae1844cb4493d532214c9b32b5e2"},
 }
 
 KERNEL_SOURCES = {"k_adj_pairs_list": ("adjoint.hip", "adjoint.hpp", "rhs_common.hpp", "common.hpp"),

@@ -319,7 +319,7 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t
 // workgroup per 64 slots.  The tests (12 instructions per candidate and 64 slots) and the
 // evaluation each bound it about as much as the search for candidates does.  One slot per
 // lane in workgroups of 256 took 234 us on 4,096 particles and 309 us on 110,592; this
-// takes 45 and 185, and with the extended terms 364 us are now 240.
+// takes 40 and 185, and with the extended terms 364 us are now 240.
 constexpr int kCellWaves = 4;
 
 template <bool kCorr, bool kExt, int P = kCellWaves>

@@ -276,16 +276,16 @@ __device__ inline double read_lane(double v, int l) {
 }
 
 // One wavefront, or kWaves of them, take 64 consecutive particles of the sorted order.  A
-// wavefront's work is a stack of ranges of siblings, each with the lanes that walk it; up to 64 ranges are taken off
-// the top at a time, one lane looking at the first node of each.  A node that even the
-// nearest point of the lanes' box accepts is a term of all the range's lanes, a node that
-// even the farthest opens is opened for all; only the nodes between are tested by each
-// lane for itself, one after the other.  Terms are gathered in LDS with their lanes and
-// added from there, one after the other, without tests or waits.  So the loads of 64
-// nodes are in flight together, and what remains is bound by the terms' arithmetic, about
-// 30 instructions each.  (A walk of one node at a time, its pointer common to the 64
-// lanes, spent half its time on the chain of loads and half its instructions on the
-// tests: 1631 us on 262,144 particles at theta 0.5; this takes 1434.)
+// wavefront's work is a stack of ranges of siblings, each with the lanes that walk it; up
+// to 64 ranges are taken off the top at a time, one lane looking at the first node of
+// each.  A node that even the nearest point of the lanes' box accepts is a term of all the
+// range's lanes, a node that even the farthest opens is opened for all; only the nodes
+// between are tested by each lane for itself, one after the other.  Terms are gathered in
+// LDS with their lanes and added from there, one after the other, without tests or waits.
+// So the loads of 64 nodes are in flight together, and what remains is bound by the terms'
+// arithmetic, about 30 instructions each.  (A walk of one node at a time, its pointer
+// common to the 64 lanes, spent half its time on the chain of loads and half its
+// instructions on the tests: 1631 us on 262,144 particles at theta 0.5; this takes 1434.)
 //
 // With several wavefronts all begin with the root; once kDeal ranges are on the stack each
 // keeps every kWaves-th of them (the terms until then are wavefront 0's), and their sums

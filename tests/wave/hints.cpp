@@ -1,0 +1,20 @@
+// The hint kernel of the pair list, run on the CPU a wavefront at a time (hip/hip_runtime.h
+// beside this file) for the test of its bounds.
+#include "hints.hpp"
+
+// Hints for the groups of a list, written as sph_build_pairs has them written.  Returns 0,
+// or 1 where a wavefront has not ended after `limit` operations across lanes.
+extern "C" int hints_run(int64_t n, const int32_t *count, const int64_t *block_start,
+                             int32_t *slot, long limit) {
+    const int64_t nb = (n + 63) / 64;
+    wave::grid = sph::blocks_for(nb, 4);
+    for (unsigned b = 0; b < wave::grid; ++b)
+        for (unsigned q = 0; q < 4; ++q)
+            if (!wave::run(b, q, limit, [&] { sph::k_pl_hints(n, count, block_start, slot); }))
+                return 1;
+    return 0;
+}
+
+// Most places and pages of a wavefront's table, most locals, words of a header, its magic.
+extern "C" const int32_t hints_limits[5] = {sph::kPageTable, sph::kMaxPages, sph::kMaxLocals,
+                                            sph::kHintHeader, sph::kHintMagic};

@@ -38,7 +38,6 @@ __device__ inline int wave_max_i32(int v) {
 // on an 8,388,608-particle non-uniform set, where it moves 13 GB.)
 constexpr int kPageTable = 512;
 constexpr int kMaxPages = 384;       // pages of a group with hints: probes stay short
-constexpr int kMaxLocals = 2047;     // locals numbered
 constexpr int kBatch = 4;            // chunks whose entries are loaded together
 
 __global__ __launch_bounds__(kBlock) void k_pl_hints(int64_t n, const int32_t *__restrict__ count,

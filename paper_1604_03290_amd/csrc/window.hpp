@@ -31,6 +31,7 @@ constexpr int kChunkSteps = 4;         // steps whose locals a lane loads at onc
 constexpr int kRoundSteps = 32;        // steps of a round
 constexpr int kMaxRounds = 64;         // rounds a header describes
 constexpr int kMaxHintRoom = 1 << 18;  // rows of a room that may hold hints
+constexpr int kMaxLocals = 2047;       // locals numbered
 
 struct HintLayout {
     int uni;    // words of the slots of the locals
@@ -145,6 +146,15 @@ __device__ inline ListBlock list_block(const ListAhead<P, W> &a) {
     return v;
 }
 
+// Place of local l in a window of W records: l mod W for the locals that are numbered, some
+// place of the window for any other l >= 0.
+template <int W>
+__host__ __device__ constexpr int window_place(int l) {
+#pragma unroll
+    for (int i = 0; i < kMaxLocals / W; ++i) l = l >= W ? l - W : l;
+    return l < W ? l : W - 1;
+}
+
 // Runs use(j, t, r) for the list steps of wavefront q (list_step): t
 // is this lane's entry and r = fetch(at) what stands at the place `at` of the window, where
 // the entry's record is if it is resident (tag[at] == t; `at` always lies inside the
@@ -177,10 +187,7 @@ __device__ inline void sweep_window(const ListBlock &v, const ListAhead<P, W> &a
         if (q + i * P < NB) fill(q + i * P, ahead.e[i]);
     auto place = [&](const ListChunk &c, int i) {
         const int w = i < 2 ? c.local.x : c.local.y;
-        int l = (i & 1) ? (int)((uint32_t)w >> 16) : w & 0xffff;
-        l = l >= W ? l - W : l;
-        l = l >= W ? l - W : l;
-        return l < W ? l : W - 1;
+        return window_place<W>((i & 1) ? (int)((uint32_t)w >> 16) : w & 0xffff);
     };
     int loaded = min(nblk, NB), r0 = 0;
     while (true) {

@@ -127,3 +127,11 @@ def test_too_many_locals(lib):
         slots = np.arange(max_locals + extra)
         rows = np.resize(slots, (36, 64)).astype(np.int32)
         assert check(lib, rows, [36] * 64, 400) == (extra == 0)
+
+
+@pytest.mark.parametrize("width", [576, 640, 704])
+def test_places_of_a_window(lib, width):
+    """Every number that is given has its place mod the window, any other a place of it."""
+    max_locals = limits(lib)[2]
+    assert [lib.window_place(width, l) for l in range(max_locals + 1)] == [l % width for l in range(max_locals + 1)]
+    assert all(0 <= lib.window_place(width, l) < width for l in range(1 << 16))

@@ -18,3 +18,13 @@ extern "C" int hints_run(int64_t n, const int32_t *count, const int64_t *block_s
 // Most places and pages of a wavefront's table, most locals, words of a header, its magic.
 extern "C" const int32_t hints_limits[5] = {sph::kPageTable, sph::kMaxPages, sph::kMaxLocals,
                                             sph::kHintHeader, sph::kHintMagic};
+
+// Place of a local in a window of `width` records (-1: no kernel has such a window).
+extern "C" int window_place(int width, int local) {
+    switch (width) {
+    case 576: return sph::window_place<576>(local);
+    case 640: return sph::window_place<640>(local);
+    case 704: return sph::window_place<704>(local);
+    default: return -1;
+    }
+}

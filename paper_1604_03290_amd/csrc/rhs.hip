@@ -39,11 +39,13 @@ __global__ __launch_bounds__(kBlock) void k_invert(const int32_t *__restrict__ p
 // dd3 / nact (null unless requested): the damage model's rates (section 3.2).  With
 // inv (user-order state, its inverse permutation) thread i takes user particle i, so
 // the state arrays are read in order and each thread writes its slot's whole 128-byte
-// record; without it (slot-ordered state) thread i takes slot i.
+// record; without it (slot-ordered state) thread i takes slot i.  mass (null unless
+// asked for): the masses in slot order.
 __global__ __launch_bounds__(kBlock) void k_prepass(GridDev g, StateDev st, int64_t n, Consts k,
                                                     double *__restrict__ rec,
                                                     int32_t *__restrict__ status, double *dd3,
-                                                    int32_t *nact, const int32_t *__restrict__ inv) {
+                                                    int32_t *nact, const int32_t *__restrict__ inv,
+                                                    double *__restrict__ mass) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int64_t s = inv ? (int64_t)inv[i] : i;
@@ -52,6 +54,7 @@ __global__ __launch_bounds__(kBlock) void k_prepass(GridDev g, StateDev st, int6
     const double d = st.d ? st.d[a] : 0.0, rho = st.rho[a], m = st.m[a];
     const double p = write_rec(g, k, s, st.x[a], st.y[a], st.z[a], st.vx[a], st.vy[a], st.vz[a],
                                rho, S, m, rec, status, st.u ? st.u[a] : 0.0, d);
+    if (mass) mass[s] = m;
     if (dd3) {
         const double f = (1.0 - d) * yield_factor(k, S);
         const double ph = p >= 0.0 ? p : (1.0 - d) * p;
@@ -192,9 +195,14 @@ __global__ __launch_bounds__(64 * P) void k_pairs64_list(GridDev g, int64_t n, C
 // The same for a list with a skin, which is built to serve many evaluations and carries
 // hints (window.hpp): a block's partner records stand in the workgroup's LDS window, each
 // loaded once instead of once per slot that names it.  The window holds the first seven
-// chunks of a record (a partner's mass is V rho) and, with the extended terms, its sound
-// speed; wavefront q takes every kFwdWaves-th chunk of four steps, whose records are read
-// from LDS one step ahead.  The kernel above is bound by its gathers (the texture
+// chunks of a record, with the extended terms all eight; wavefront q takes every
+// kFwdWaves-th chunk of four steps, whose records are read
+// from LDS one step ahead.  The mass alone comes from memory by the entry (mass: [n] in slot
+// order), two chunks ahead: the address unit is idle here, and an eighth LDS read a step
+// costs more (V rho in the mass's place is one rounding off; right-hand side of 262,144
+// particles with V rho 160 us, with the mass from memory 166, from the window 171; with the
+// extended terms, whose registers do not allow it, 213 with V rho and 223 from the window).
+// The kernel above is bound by its gathers (the texture
 // addresser takes 64 B a clock and CU at best: 112 B a pair), this one by the pairs' FP64
 // arithmetic and LDS reads (118 and 73 cycles a step and CU): 262,144 particles with a
 // skin of 0.15 spacings 172 us of gathers, 121 here; with the extended terms 222 and 162;
@@ -208,10 +216,11 @@ template <bool kCorr, bool kExt, int P = kFwdWaves>
 __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t n, Consts k,
                                                                    const double *__restrict__ rec,
                                                                    StateDev st, OutDev out,
-                                                                   double *__restrict__ Lout) {
-    constexpr int W = kExt ? 640 : 704;  // two workgroups per CU
-    __shared__ double2 ring[W * 7];
-    __shared__ double cs[kExt ? W : 1];
+                                                                   double *__restrict__ Lout,
+                                                                   const double *__restrict__ mass) {
+    constexpr int W = kExt ? 576 : 704;  // two workgroups per CU
+    __shared__ double2 ring[W * (kExt ? 8 : 7)];
+    double2 *const last = ring + W * 7;  // with kExt the records' last chunks: mass, sound speed
     __shared__ int32_t tag[W];
     const int64_t w = xcd_list_block(gridDim.x);
     const int64_t w0 = w * 64;
@@ -236,7 +245,7 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t
     const char *recs = reinterpret_cast<const char *>(rec);
     struct Partner {
         double2 b[7];
-        double c;
+        double c, m;
         int32_t tag;
     };
     auto ready = [&] {
@@ -249,7 +258,10 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t
                 const double2 *m = rec2(rec, t);
 #pragma unroll
                 for (int i = 0; i < 7; ++i) r.b[i] = m[i];
-                if constexpr (kExt) r.c = m[7].y;
+                if constexpr (kExt) {
+                    r.m = m[7].x;
+                    r.c = m[7].y;
+                }
             }
             wait_vm();  // here, or every step would wait for its prefetch
         }
@@ -260,8 +272,8 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t
             const double Tb[6] = {b4.x, b4.y, b5.x, b5.y, b6.x, b6.y};
             pair64<kCorr, kExt>(k, d2, xa - b0.x, ya - b0.y, za - b1.x, b1.y - vxa, b2.x - vya,
                                 b2.y - vza, rho_a, b3.x, p4.x + b4.x, p4.y + b4.y, p5.x + b5.x,
-                                p5.y + b5.y, p6.x + b6.x, p6.y + b6.y, b3.y * b3.x, b3.y, acc, Ta,
-                                Tb, tens_a, c_a, r.c);
+                                p5.y + b5.y, p6.x + b6.x, p6.y + b6.y, r.m, b3.y, acc, Ta, Tb,
+                                tens_a, c_a, r.c);
         }
     };
     // A dense group whose partners do not fit the window at once: while the chip is full
@@ -269,24 +281,29 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t
     // such groups gathered); a smaller launch waits for the few densest groups, and then
     // the gathers are the shorter (12,000 to 30,000 particles 81 us against 95).
     if (v.locals && (v.locals <= W || gridDim.x > kManyGroups)) {
-        sweep_window(
+        sweep_window<P, W, !kExt>(
             v, ahead, tag, n,
             [&](int p, int e) {
                 gather_dma<7>(recs, kRec * 8, e, ring + p * 64 * 7);
-                if constexpr (kExt) cs[64 * p + __lane_id()] = rec2(rec, e)[7].y;
+                if constexpr (kExt) last[64 * p + __lane_id()] = rec2(rec, e)[7];
             },
-            ready,
+            [&](int t) { return mass[t]; }, ready,
             [&](int at) {
                 Partner r;
 #pragma unroll
                 for (int i = 0; i < 7; ++i) r.b[i] = ring[7 * at + i];
-                r.c = kExt ? cs[at] : 0.0;
+                if constexpr (kExt) {
+                    const double2 b7 = last[at];
+                    r.m = b7.x;
+                    r.c = b7.y;
+                }
                 r.tag = tag[at];
                 return r;
             },
             use);
     } else {
         ready();
+        static_assert(sizeof ring >= P * 64 * 8 * 16, "a step's records for each wavefront");
         double2 *buf = ring + (threadIdx.x >> 6) * 64 * 8;
         sweep_gather<P>(
             v, [&](int e) { gather_dma8(recs, kRec * 8, e, buf); },
@@ -294,7 +311,9 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t
                 Partner r;
 #pragma unroll
                 for (int i = 0; i < 7; ++i) r.b[i] = dma8_chunk(buf, i);
-                r.c = kExt ? dma8_chunk(buf, 7).y : 0.0;
+                const double2 b7 = dma8_chunk(buf, 7);
+                r.m = b7.x;
+                r.c = b7.y;
                 return r;
             },
             use);
@@ -306,6 +325,23 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t
         if (Lout) store_vgrad<kCorr>(Lout, s, acc.L, acc.M);
     }
 }
+
+// What the pair terms need of a partner's last chunk: its mass and, with the extended
+// terms, its signed sound speed.
+template <bool kExt>
+struct LastChunk {
+    double m;
+    LastChunk() = default;
+    __device__ explicit LastChunk(double2 b) : m(b.x) {}
+    __device__ double c() const { return 0.0; }
+};
+template <>
+struct LastChunk<true> {
+    double m, s;
+    LastChunk() = default;
+    __device__ explicit LastChunk(double2 b) : m(b.x), s(b.y) {}
+    __device__ double c() const { return s; }
+};
 
 // FP64 pair sums straight from the cells: a workgroup of kCellWaves wavefronts takes 64
 // slots, in the parts of sweep.hpp.  Their candidates, the slots of the cells around a
@@ -327,10 +363,13 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_cells(GridDev g, int64_t 
                                                                   const double *__restrict__ rec,
                                                                   StateDev st, OutDev out,
                                                                   double *__restrict__ Lout) {
-    constexpr int W = 640, kOwn = W / P, kWords = (kOwn + 63) / 64;  // two workgroups per CU
+    using Last = LastChunk<kExt>;
+    constexpr int W = kExt ? 576 : 640;  // two workgroups per CU
+    constexpr int kOwn = W / P, kWords = (kOwn + 63) / 64;
     constexpr int kBlocks = W / 64, kMine = (kBlocks + P - 1) / P;
+    static_assert(64 * P <= W, "a round of candidates fits");
     __shared__ double2 ring[W * 7];
-    __shared__ double cs[kExt ? W : 1];
+    __shared__ Last last[W];
     __shared__ int32_t tag[W];
     __shared__ int32_t run_s0[kRunCap], run_pre[kRunCap];
     __shared__ int32_t pass[4], kept[2][P];
@@ -353,7 +392,7 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_cells(GridDev g, int64_t 
     const bool tens_a = kExt && signbit(c_a);
     struct Partner {
         double2 b[7];
-        double c;
+        Last l;
     };
     auto use = [&](const Partner &r, bool on) {
         const double2 b0 = r.b[0], b1 = r.b[1], b2 = r.b[2], b3 = r.b[3], b4 = r.b[4], b5 = r.b[5],
@@ -363,8 +402,8 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_cells(GridDev g, int64_t 
             const double Tb[6] = {b4.x, b4.y, b5.x, b5.y, b6.x, b6.y};
             pair64<kCorr, kExt>(k, d2, xa - b0.x, ya - b0.y, za - b1.x, b1.y - vxa, b2.x - vya,
                                 b2.y - vza, rho_a, b3.x, p4.x + b4.x, p4.y + b4.y, p5.x + b5.x,
-                                p5.y + b5.y, p6.x + b6.x, p6.y + b6.y, b3.y * b3.x, b3.y, acc, Ta,
-                                Tb, tens_a, c_a, r.c);
+                                p5.y + b5.y, p6.x + b6.x, p6.y + b6.y, r.l.m, b3.y, acc, Ta, Tb,
+                                tens_a, c_a, r.l.c());
         }
     };
     GroupParts parts(g, act, act ? s : w0, xa, ya, za, k.reach);
@@ -385,7 +424,7 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_cells(GridDev g, int64_t 
                         if (!(dist2_exact(xa, ya, za, r.b[0].x, r.b[0].y, r.b[1].x) < k.h2)) continue;
 #pragma unroll
                         for (int c = 2; c < 7; ++c) r.b[c] = rb[c];
-                        r.c = kExt ? rb[7].y : 0.0;
+                        r.l = Last(rb[7]);
                         use(r, true);
                     }
                 });
@@ -405,13 +444,17 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_cells(GridDev g, int64_t 
                 any[i] = __ballot(there) != 0;
                 if (there && (uint32_t)(e[i] - (int)w0) < 64u) self[e[i] - (int)w0] = at;
             }
+            Last l[kMine];  // all asked for before any is waited for
 #pragma unroll
             for (int i = 0; i < kMine; ++i)
                 if (any[i]) {
-                    const int b = q + i * P;
-                    gather_dma<7>(reinterpret_cast<const char *>(rec), kRec * 8, e[i], ring + b * 64 * 7);
-                    if constexpr (kExt) cs[64 * b + lane] = rec2(rec, e[i])[7].y;
+                    gather_dma<7>(reinterpret_cast<const char *>(rec), kRec * 8, e[i],
+                                  ring + (q + i * P) * 64 * 7);
+                    l[i] = Last(rec2(rec, e[i])[7]);
                 }
+#pragma unroll
+            for (int i = 0; i < kMine; ++i)
+                if (any[i]) last[64 * (q + i * P) + lane] = l[i];
             wait_vm();
             __syncthreads();
             const int mq = m > q ? (m - q + P - 1) / P : 0;
@@ -460,7 +503,7 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_cells(GridDev g, int64_t 
                 Partner r;
 #pragma unroll
                 for (int c = 0; c < 7; ++c) r.b[c] = own[7 * at + c];
-                r.c = kExt ? cs[q * kOwn + at] : 0.0;
+                r.l = last[q * kOwn + at];
                 return r;
             };
             Partner r = fetch();
@@ -692,7 +735,7 @@ int invert_launch(const GridDev &g, int64_t n, int32_t *inv, hipStream_t s) {
 }
 
 int prepass_launch(const GridDev &g, const StateDev &st, int64_t n, const Consts &k, double *rec,
-                   int32_t *status, hipStream_t s, const OutDev *od, int32_t *inv) {
+                   int32_t *status, hipStream_t s, const OutDev *od, int32_t *inv, double *mass) {
     if (g.io && inv) {
         k_invert<<<blocks_for(n), kBlock, 0, s>>>(g.io, n, inv);
         SPH_LAUNCHED();
@@ -700,7 +743,7 @@ int prepass_launch(const GridDev &g, const StateDev &st, int64_t n, const Consts
         inv = nullptr;
     }
     k_prepass<<<blocks_for(n), kBlock, 0, s>>>(g, st, n, k, rec, status, od ? od->dd3 : nullptr,
-                                               od ? od->n_act : nullptr, inv);
+                                               od ? od->n_act : nullptr, inv, mass);
     SPH_LAUNCHED();
     return SPH_OK;
 }
@@ -792,10 +835,18 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
     StateDev st = state_dev(state);
     OutDev od = out_dev(out);
     int rc;
+    if (rec_ready && !slot_state)
+        return fail(SPH_ERR_NOT_IMPLEMENTED, "records without a prepass need a slot-ordered state");
     if (od.dd3 && rec_ready)
         return fail(SPH_ERR_NOT_IMPLEMENTED, "damage rates need the prepass");
-    if (!rec_ready && (rc = prepass_launch(g, st, n, k, rec, c.status(), s, &od, inv))) return rc;
     const bool ext = k.eps_s > 0.0 || od.du || od.dx || k.eos != 0;
+    const bool window = g.pl_count && grid->pairs->skin > 0.0;
+    // masses in slot order for the window kernel, where the FP32 records would be
+    const double *mass = state->m;
+    double *to = nullptr;
+    if (precision == SPH_FP64 && window && !ext && !slot_state)
+        mass = to = reinterpret_cast<double *>(r32);
+    if (!rec_ready && (rc = prepass_launch(g, st, n, k, rec, c.status(), s, &od, inv, to))) return rc;
     if (precision == SPH_FP64) {
         TimedRegion t(timed ? "pairs_fp64" : nullptr, s);
         auto launch = [&](auto corr, auto extra) {
@@ -803,8 +854,8 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
             auto with = [&](auto waves) {
                 constexpr int P = decltype(waves)::value;
                 const dim3 gb(blocks_for(n, 64)), tb(64 * P);
-                if (g.pl_count && grid->pairs->skin > 0.0)
-                    k_pairs64_window<C, E, P><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out);
+                if (window)
+                    k_pairs64_window<C, E, P><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out, mass);
                 else if (g.pl_count)
                     k_pairs64_list<C, E, P><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out);
                 else

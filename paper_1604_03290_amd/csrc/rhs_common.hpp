@@ -117,10 +117,10 @@ inline OutDev out_dev(const sph_deriv *o) {
 // with T = sigma / rho^2 (xx, yy, zz, xy, xz, yz), V = m / rho and c the sound
 // speed, negated (sign bit set, also for 0) when the pressure is negative: the
 // artificial stress's tension test.  A partner's
-// first seven 16-byte chunks carry everything its pair terms need (its mass being
-// V rho), which the adjoint's gathers use; the forward kernels read all eight (the
-// eighth also holds the sound speed c, which other equations of state than the
-// liquid one vary per particle).
+// first seven 16-byte chunks carry everything the adjoint's pair terms need (its mass as
+// V rho), which its gathers use; the forward sums take the mass as it is, from the eighth
+// chunk (which also holds the sound speed c, which other equations of state than the
+// liquid one vary per particle) or, in the window kernel, from an array of the masses.
 constexpr int kRec = 16;
 // FP32 record, 80 bytes per slot: FP64 position (for the exact partner test and
 // the differences) and the FP32 operands:
@@ -915,9 +915,10 @@ int invert_launch(const GridDev &g, int64_t n, int32_t *inv, hipStream_t s);
 // od (nullable): outputs whose dd3 / n_act, when set, receive the damage rates
 // inv (nullable): n int32 of scratch; with a user-ordered state the prepass fills it with
 // the inverse permutation and reads the state in user order
+// mass (nullable): [n], the masses in slot order
 int prepass_launch(const GridDev &g, const StateDev &st, int64_t n, const Consts &k, double *rec,
                    int32_t *status, hipStream_t s, const OutDev *od = nullptr,
-                   int32_t *inv = nullptr);
+                   int32_t *inv = nullptr, double *mass = nullptr);
 int check_state(const sph_grid *grid, const sph_state *st);
 int check_params(const sph_grid *grid, const sph_params *pr);
 int check_deriv(const sph_deriv *o);
@@ -925,7 +926,7 @@ int check_deriv(const sph_deriv *o);
 // followed with the correction by its moment matrix M, 6 arrays (xx yy zz xy xz yz).
 // slot_state: the state and output arrays are in the grid's slot order.
 // rec_ready: the operand records (the first carve, rhs_rec_of) already hold the
-// state's records, so the prepass is skipped.
+// state's records, so the prepass is skipped (with slot_state only).
 // timed: bracket the pair kernel for the diagnostic timing table when it is enabled.
 int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *params,
                int precision, const sph_deriv *out, Carve &c, hipStream_t s,

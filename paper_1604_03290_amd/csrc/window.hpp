@@ -158,21 +158,26 @@ __host__ __device__ constexpr int window_place(int l) {
 // Runs use(j, t, r) for the list steps of wavefront q (list_step): t
 // is this lane's entry and r = fetch(at) what stands at the place `at` of the window, where
 // the entry's record is if it is resident (tag[at] == t; `at` always lies inside the
-// window).  A step is fetched while the one before it is evaluated.  The window holds
+// window).  A step is fetched while the one before it is evaluated.  With kMass
+// r.m = mass(t) besides, which comes from memory by the entry itself: a chunk's are asked
+// for while the chunk before it is evaluated, and its entries a chunk earlier.  The window holds
 // W records, in blocks of 64: load(p, e) starts the loads of the 64 records of slots e (one
 // per lane) into places 64 p .. 64 p + 63.  Locals go to places local mod W; a block of
 // locals is loaded once every step below has been done that may need what it replaces.
-// ready() is called once, when the first records have arrived.  Every thread of the workgroup calls it; on return the window may still be read by others.
-template <int P, int W, class Load, class Ready, class Fetch, class Use>
+// ready() is called once, when the first records have arrived.  Every thread of the workgroup
+// calls it; on return the window may still be read by others.
+template <int P, int W, bool kMass, class Load, class Mass, class Ready, class Fetch, class Use>
 __device__ inline void sweep_window(const ListBlock &v, const ListAhead<P, W> &ahead,
-                                    int32_t *tag, int64_t n, Load &&load, Ready &&ready,
-                                    Fetch &&fetch, Use &&use) {
+                                    int32_t *tag, int64_t n, Load &&load, Mass &&mass,
+                                    Ready &&ready, Fetch &&fetch, Use &&use) {
     static_assert(W % 64 == 0, "the window holds whole blocks of records");
     constexpr int NB = W / 64, kRoundChunks = kRoundSteps / kChunkSteps / P;
     static_assert(kRoundChunks >= 1, "a round is one or more chunks of every wavefront");
+    constexpr int kAhead = kMass ? 2 : 1;  // chunks asked for ahead of the one evaluated
     const int lane = __lane_id();
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    ListChunk cur = ahead.chunk;
+    ListChunk cur = ahead.chunk, next = cur;
+    if constexpr (kMass) next = list_chunk<P>(v, q, 1, v.steps);
     const int nblk = (v.locals + 63) >> 6;
     const int rounds = max(1, (v.steps + kRoundSteps - 1) / kRoundSteps);
     auto fill = [&](int k, int e) {  // block k of the locals, e: this lane's slot of it
@@ -185,6 +190,12 @@ __device__ inline void sweep_window(const ListBlock &v, const ListAhead<P, W> &a
 #pragma unroll
     for (int i = 0; i < ListAhead<P, W>::kOwn; ++i)
         if (q + i * P < NB) fill(q + i * P, ahead.e[i]);
+    double m[kChunkSteps];
+    if constexpr (kMass) {
+#pragma unroll
+        for (int i = 0; i < kChunkSteps; ++i)  // (the first chunk was read up to the room)
+            m[i] = mass(list_step<P>(q, 0, i) < v.steps ? cur.t[i] : 0);
+    }
     auto place = [&](const ListChunk &c, int i) {
         const int w = i < 2 ? c.local.x : c.local.y;
         return window_place<W>((i & 1) ? (int)((uint32_t)w >> 16) : w & 0xffff);
@@ -203,14 +214,27 @@ __device__ inline void sweep_window(const ListBlock &v, const ListAhead<P, W> &a
         if (c < c1 && list_step<P>(q, c, 0) < v.steps) {
             auto rec = fetch(place(cur, 0));
             for (; c < c1 && list_step<P>(q, c, 0) < v.steps; ++c) {
-                const ListChunk next = list_chunk<P>(v, q, c + 1, v.steps);
+                const ListChunk after = list_chunk<P>(v, q, c + kAhead, v.steps);
+                double mn[kChunkSteps];
+                if constexpr (kMass) {
+#pragma unroll
+                    for (int i = 0; i < kChunkSteps; ++i) mn[i] = mass(next.t[i]);
+                } else {
+                    next = after;
+                }
 #pragma unroll
                 for (int i = 0; i < kChunkSteps; ++i) {
                     const auto then = fetch(i + 1 < kChunkSteps ? place(cur, i + 1) : place(next, 0));
+                    if constexpr (kMass) rec.m = m[i];
                     use(list_step<P>(q, c, i), cur.t[i], rec);
                     rec = then;
                 }
                 cur = next;
+                if constexpr (kMass) {
+                    next = after;
+#pragma unroll
+                    for (int i = 0; i < kChunkSteps; ++i) m[i] = mn[i];
+                }
             }
         }
         if (r1 == rounds) return;

@@ -81,9 +81,9 @@ enum sph_op {
  * lanes of the last group past n), so every entry of those steps is a valid slot.
  * The group's room, block_start[B + 1] - block_start[B], is 64 times the largest
  * upper bound of its slots' counts and may exceed 64 times its steps; what lies past
- * the steps is the library's own (with a skin, hints from which its kernels find the same
- * entries' records faster; they count for nothing where they do not agree with the entries, and
- * need not be copied with them).  All arrays are device arrays owned by the caller. */
+ * the steps is the library's own (with a skin and up to about 180 candidates a slot, hints from which the
+ * FP64 right-hand side finds the same entries' records faster; they count for nothing where
+ * they do not agree with the entries, and need not be copied with them).  All arrays are device arrays owned by the caller. */
 typedef struct {
     int64_t n;             /* slots */
     double radius;         /* h + skin at build time */
@@ -91,7 +91,8 @@ typedef struct {
     int32_t *count;        /* [n] candidates per slot */
     int64_t *block_start;  /* [ceil(n / 64) + 1] first entry of each group; last = total */
     int32_t *slot;         /* [capacity] candidate slots, interleaved by 64 */
-    int64_t capacity;
+    int64_t capacity;      /* also tells how dense the set is (capacity / n): the kernels are
+                              chosen by it, so far more than the list needs costs speed */
     double *x0;            /* [3 n] slot-ordered positions at build time (x, y, z per slot) */
     int32_t *partners;     /* [n] or NULL: partners of each slot at build time (distance
                               below the grid's h), counted by the fill */

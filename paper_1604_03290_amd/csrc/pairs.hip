@@ -256,7 +256,7 @@ extern "C" int sph_build_pairs(sph_grid *grid, const double *x, const double *y,
     k_pl_fill<<<blocks_for(nb, kBlock / 64), kBlock, 0, s>>>(g, x0, n, r2, reach, count,
                                                               block_start, slot, h2, partners);
     SPH_LAUNCHED();
-    if (grid->skin > 0.0) {  // (the kernels that read the hints are chosen by the skin too)
+    if (through_window(*grid, capacity, false, false)) {  // (the plain sums: first to go there)
         k_pl_hints<<<blocks_for(nb, kBlock / kWave), kBlock, 0, s>>>(n, count, block_start, slot);
         SPH_LAUNCHED();
     }

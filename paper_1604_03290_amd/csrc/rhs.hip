@@ -210,7 +210,6 @@ __global__ __launch_bounds__(64 * P) void k_pairs64_list(GridDev g, int64_t n, C
 // Without a skin the hints are not built: they cost 83 us on 262,144 particles, more than
 // the 51 us of one evaluation, and such a list holds for one set of positions only.
 constexpr int kFwdWaves = 4;
-constexpr unsigned kManyGroups = 1024;
 
 template <bool kCorr, bool kExt, int P = kFwdWaves>
 __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t n, Consts k,
@@ -277,9 +276,10 @@ __global__ __launch_bounds__(64 * P, 2) void k_pairs64_window(GridDev g, int64_t
         }
     };
     // A dense group whose partners do not fit the window at once: while the chip is full
-    // its reloads and barriers are hidden (100,000 non-uniform particles 149 us, 163 with
-    // such groups gathered); a smaller launch waits for the few densest groups, and then
-    // the gathers are the shorter (12,000 to 30,000 particles 81 us against 95).
+    // its reloads and barriers are hidden (300,000 particles with 143 partners 308 us, 397
+    // with such groups gathered here); a smaller launch waits for the few densest groups,
+    // and then the gathers are the shorter (12,000 to 30,000 non-uniform particles 81 us
+    // against 95).
     if (v.locals && (v.locals <= W || gridDim.x > kManyGroups)) {
         sweep_window<P, W, !kExt>(
             v, ahead, tag, n,
@@ -840,7 +840,8 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
     if (od.dd3 && rec_ready)
         return fail(SPH_ERR_NOT_IMPLEMENTED, "damage rates need the prepass");
     const bool ext = k.eps_s > 0.0 || od.du || od.dx || k.eos != 0;
-    const bool window = g.pl_count && grid->pairs->skin > 0.0;
+    const bool skin = g.pl_count && grid->pairs->skin > 0.0;
+    const bool window = skin && through_window(*grid, grid->pairs->capacity, k.corr, ext);
     // masses in slot order for the window kernel, where the FP32 records would be
     const double *mass = state->m;
     double *to = nullptr;
@@ -862,7 +863,14 @@ int rhs_launch(const sph_grid *grid, const sph_state *state, const sph_params *p
                     k_pairs64_cells<C, E, P><<<gb, tb, 0, s>>>(g, n, k, rec, st, od, L_out);
             };
             static_assert(kFwdWaves == kSplit && kCellWaves == kSplit, "one choice for all three");
-            if (blocks_for(n, 64) <= kFewBlocks)
+            // A dense list's plain sums keep eight wavefronts up to four blocks a CU: with
+            // four all blocks stand on the CUs from the start, and the launch waits for the
+            // CU with the most dense ones.  (us with four and eight: 20,000 non-uniform
+            // particles 61 and 50, 40,000 108 and 93, 50,000 109 and 113, 65,000 140 and
+            // 120; 64,000 with 285 candidates 129 and 130; with the extended terms 40,000
+            // with 142 candidates 77 and 84: their eight wavefronts leave one workgroup a CU.)
+            const unsigned few = skin && !window && !C && !E ? kManyGroups : kFewBlocks;
+            if (blocks_for(n, 64) <= few)
                 with(std::integral_constant<int, 2 * kSplit>{});
             else
                 with(std::integral_constant<int, kSplit>{});

@@ -49,6 +49,48 @@ __host__ __device__ inline HintLayout hint_layout(int64_t room_rows, const int32
     return h;
 }
 
+// Candidates of a slot of a list with this many entries of room, on average: what a slot is
+// given room for are the slots of the cells within reach of it, in a set that fills space
+// those of the volume that a ball of that reach has swept over by a cell.  (Lattices with 69
+// to 278 candidates: 69 to 293.)
+inline double mean_candidates(const sph_grid &g, int64_t entries) {
+    constexpr double pi = 3.14159265358979323846;
+    const double r = g.h + g.skin, a = g.cell, b = r + 0.5 * g.skin;
+    const double swept = a * a * a + 6.0 * a * a * b + 3.0 * pi * a * b * b + 4.0 / 3.0 * pi * b * b * b;
+    return (double)entries / (double)g.n * (4.0 / 3.0 * pi * r * r * r) / swept;
+}
+
+// Whether the FP64 sums over a list with a skin go through the window (k_pairs64_window) or
+// are gathered (k_pairs64_list), by how dense the set is (entries: the list's capacity; one
+// larger than the list needs costs speed only).  A block of 64 slots with more than about 140
+// candidates each names more partners than a window holds.  Up to kManyGroups blocks
+// (four a CU) such a block is gathered with the window's LDS unused, which leaves two
+// workgroups a CU instead of four; beyond, its window is filled again and again, hidden
+// behind the other blocks until the sets are denser still.  The extended terms' window holds
+// fewer records, and their kernel has no registers left to read ahead.  us, window and list,
+// with a skin of 0.15 spacings:
+//                              40,000 particles   80,000       200,000
+//   plain     111 candidates   50.0  50.7         68.6  80.4   152.6 168.0
+//             142              68.4  60.5         91.2 101.7   194.6 208.1
+//             172              82.9  69.7        109.2 118.3   239.0 245.5
+//             188, non-uniform 93.8 108.3        170.9 145.6   328.3 324.8  (middle: 90,000)
+//             285             121.4 100.6        182.3 177.2   390.4 370.5
+//   corrected 142              67.6  60.7         95.0  93.5   203.5 215.9
+//             172              84.7  70.0        114.2 108.7   249.6 254.7
+//   extended   98              56.0  56.7         86.5  83.8   179.3 185.1
+//             113              65.6  64.4        102.5  95.3   222.3 213.2
+//   both       77              54.5  55.0         83.4  81.6   174.3 179.3
+//              98              58.6  56.9         91.6  84.3   193.4 187.1
+// Where no form goes through the window no hints are built: 262,144 non-uniform particles'
+// list took 1,014 us with them.
+constexpr unsigned kManyGroups = 1024;
+
+inline bool through_window(const sph_grid &g, int64_t entries, bool corr, bool ext) {
+    const bool few = (g.n + 63) / 64 <= kManyGroups;
+    const double most = ext ? (corr ? 90.0 : 110.0) : few ? 125.0 : corr ? 150.0 : 180.0;
+    return g.skin > 0.0 && mean_candidates(g, entries) < most;
+}
+
 // A block of the pair list as one wavefront sees it.
 struct ListBlock {
     const int32_t *row;  // this lane's entry of step j at row[64 j]

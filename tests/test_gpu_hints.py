@@ -1,7 +1,11 @@
 """Hints of a pair list at their limits: the groups that get none because they name too many
-pages or slots (tests/test_hints_host.py has the same limits on the CPU), and the groups whose
-partners do not fit the LDS window at once.  The hints never change a bit of the sums, so
-every case is compared, bit for bit, with the same list without them."""
+pages or slots (tests/test_hints_host.py has the same limits on the CPU), the groups whose
+partners do not fit the LDS window at once, and the lists too dense for the window.  The
+hints never change a bit of the sums, so the sums are compared, bit for bit, with those of
+the same list without them.
+
+Single particles far apart are added to the small dense sets: a launch of more than 1,024
+groups with few candidates on average goes through the window with all its groups."""
 import numpy as np
 import pytest
 import torch
@@ -37,6 +41,20 @@ def dust(in_reach):
     return np.ascontiguousarray(np.concatenate(pos, axis=1))
 
 
+def single(n, z0, pitch):
+    """Positions of n particles without partners, from z0 on."""
+    i = np.arange(n)
+    return np.stack([i % 20, i // 20 % 5, i // 100]) * pitch + np.array([[1.0], [1.0], [z0]])
+
+
+def state(pos, seed):
+    rng = np.random.default_rng(seed)
+    n = pos.shape[1]
+    arrays = (np.ascontiguousarray(pos), rng.normal(size=(3, n)), 2700.0 * rng.uniform(0.99, 1.01, n),
+              1e7 * rng.normal(size=(6, n)), rng.uniform(1.0, 2.0, n))
+    return P.ParticleState.from_arrays(*arrays, "cuda")
+
+
 # cells of 1: h + skin = 2; (in reach per cell, most pages after a chunk of four steps)
 DUST = {
     "all fit": [2, 2, 1, 1, 1, 1] + [0] * 10,         # 128, 384
@@ -47,16 +65,26 @@ DUST = {
 
 def dust_grid(name):
     pos = dust(DUST[name])
-    n = pos.shape[1]
-    rng = np.random.default_rng(8)
-    w = W.cube(4, 1.0 / 16, 1)
-    params = dict(w.params, h=1.9, dmpd=0.8)
-    arrays = (pos, rng.normal(size=(3, n)), 2700.0 * rng.uniform(0.99, 1.01, n),
-              1e7 * rng.normal(size=(6, n)), rng.uniform(1.0, 2.0, n))
-    st = P.ParticleState.from_arrays(*arrays, "cuda")
-    box = (np.zeros(3), np.array([63.9, 15.9, 31.9]))
-    g = P.sph_build_cells(st.pos, 1.9, skin=0.1, cells_per_h=2, box=box, pairs=True)
-    return g, st, params
+    dusty = pos.shape[1] // 64 - 1  # the dust's group: its blocks of cells follow the layer's
+    st = state(np.concatenate([pos, single(66000, 40.0, 2.2)], axis=1), 8)
+    params = dict(W.cube(4, 1.0 / 16, 1).params, h=1.9, dmpd=0.8)
+    box = (np.zeros(3), np.array([63.9, 15.9, 1500.0]))
+    return P.sph_build_cells(st.pos, 1.9, skin=0.1, cells_per_h=2, box=box, pairs=True), st, params, dusty
+
+
+FORMS = [(False, False), (True, False), (False, True), (True, True)]
+
+
+def form(params, extra, correction):
+    return dict(params, correction=float(correction), **(dict(eps_s=0.2, xsph=0.5) if extra else {}))
+
+
+def block(side, h_over_dx, skin, lone, seed=3):
+    """A block of side^3 particles and so many single ones: grid with its list, state, params."""
+    w = W.cube(side, 1.0, seed, h_over_dx=h_over_dx)
+    pos = np.concatenate([w.pos, single(lone, 4.0 * side, 1.1 * (w.h + skin))], axis=1) if lone else w.pos
+    st = state(pos, seed)
+    return P.sph_build_cells(st.pos, w.h, skin=skin, cells_per_h=2, pairs=True), st, w.params
 
 
 def lists(g):
@@ -100,6 +128,7 @@ def wipe(g):
 
 
 def sums(g, st, params, extra=False):
+    """FP64 outputs as arrays."""
     out = P.sph_rhs(g, st, params, "fp64", extra=extra)
     assert P.workspace_status(out["_ws"]) == 0
     keys = ("acc", "drho", "dS", "rho_sum") + (("du", "xv") if extra else ())
@@ -117,28 +146,73 @@ def same_without_hints(g, st, params, extra=False):
 
 @pytest.mark.parametrize("name", list(DUST))
 def test_pages(name):
-    g, st, params = dust_grid(name)
-    last = g.n // 64 - 1  # the dust, whose blocks of cells lie above the layer's
-    rows = named(g, last)
+    g, st, params, dusty = dust_grid(name)
+    rows = named(g, dusty)
     after = [distinct(rows[:k] >> 4) for k in range(4, rows.shape[0] + 4, 4)]
     want = {"all fit": [128, 384], "too many pages": [256, 512], "no free place": [128, 384, 640]}
     assert after == want[name]
     h = headers(g)
-    assert (h[last] > 0) == (after[-1] <= PAGES)
-    assert h[:last].any()  # the layer's groups, where their room leaves some
+    assert (h[dusty] > 0) == (after[-1] <= PAGES)
+    assert h[:dusty].any()  # the layer's groups, where their room leaves some
     same_without_hints(g, st, params)
 
 
-@pytest.mark.parametrize("extra", [False, True])
-def test_more_slots_than_numbered(extra):
-    """About a thousand partners a slot: some groups name more than 2,047 slots, some fewer."""
-    w = W.cube(19, 1.0 / 16, 3, h_over_dx=6.2)
-    st = P.ParticleState.from_arrays(w.pos, w.vel, w.rho, w.S, w.m, "cuda")
-    g = P.sph_build_cells(st.pos, w.h, skin=0.05 * w.dx, cells_per_h=2, pairs=True)
+@pytest.mark.parametrize("extra,correction", FORMS)
+def test_many_windows(extra, correction):
+    """About a thousand partners a slot: groups of up to four windows (576 records with the
+    extended terms, 704 without), and groups that name more than 2,047 slots."""
+    g, st, params = block(19, 6.2, 0.05, 90000)
     h, c = headers(g), lists(g)[0]
-    slots = np.array([distinct(named(g, i)) for i in range(len(c))])
-    many = slots > LOCALS
-    assert many.any() and not many.all()
-    assert not h[many].any()
-    assert ((h == slots) | (h == 0)).all() and (h > 1500).any()
-    same_without_hints(g, st, dict(w.params, eps_s=0.2, xsph=0.5) if extra else w.params, extra)
+    dense = np.flatnonzero(c.max(1) > 100)
+    slots = np.array([distinct(named(g, i)) for i in dense])
+    assert not h[dense][slots > LOCALS].any() and (slots > LOCALS).any()
+    kept = h[dense][h[dense] > 0]
+    assert set(kept) <= set(slots) and (kept > 1920).any() and (kept < 1408).any()
+    same_without_hints(g, st, form(params, extra, correction), extra)
+
+
+@pytest.mark.parametrize("side,h_over_dx,hints", [(12, 2.4, True), (12, 3.9, False), (41, 3.1, True),
+                                                  (41, 3.9, False)])
+def test_dense_lists_have_none(side, h_over_dx, hints):
+    """About 76 candidates a slot, 285, and between them in a launch that fills the chip."""
+    g = block(side, h_over_dx, 0.15, 0)[0]
+    assert headers(g).any() == hints
+
+
+# 343 groups (the gathers' plain sums with eight wavefronts a group, the others with four),
+# 1,077 (all with four) and, with 113 candidates, the window at 1,024 groups exactly and one more
+@pytest.mark.parametrize("side,h_over_dx,take", [(28, 3.9, None), (41, 3.9, None), (41, 2.8, 65536),
+                                                 (41, 2.8, 65537)])
+@pytest.mark.parametrize("extra,correction", FORMS)
+def test_list_and_cells_agree(side, h_over_dx, take, extra, correction):
+    """The same terms in other orders, as in the test of the sums from the cells: 1e-12 of the
+    largest output, 1e-10 with the correction's inverse."""
+    w = W.cube(side, 1.0 / 16, 5, h_over_dx=h_over_dx)
+    if take:
+        w = w.take(np.arange(take))
+    st = P.ParticleState.from_arrays(w.pos, w.vel, w.rho, w.S, w.m, "cuda")
+    got = [sums(P.sph_build_cells(st.pos, w.h, skin=0.15 * w.dx, cells_per_h=2, pairs=pairs), st,
+                form(w.params, extra, correction), extra) for pairs in (False, True)]
+    for k, v in got[1].items():
+        assert np.isfinite(v).all(), k
+        assert np.abs(got[0][k] - v).max() <= (1e-10 if correction else 1e-12) * np.abs(v).max(), k
+
+
+@pytest.mark.parametrize("extra", [False, True])
+def test_changed_entries_count(extra):
+    """Entries of other slots written over the list's, its hints left as they were: the sums
+    are those of the entries, as the same list without hints gives them."""
+    w = W.cube(17, 1.0 / 16, 3)
+    st = P.ParticleState.from_arrays(w.pos, w.vel, w.rho, w.S, w.m, "cuda")
+    g = P.sph_build_cells(st.pos, w.h, skin=0.15 * w.dx, cells_per_h=2, pairs=True)
+    params = form(w.params, extra, False)
+    before, h = sums(g, st, params, extra), headers(g)
+    assert (h > 0).all()
+    c, b, s = lists(g)
+    for i in range(len(c)):  # a slot's second entry over its first
+        for lane in np.flatnonzero(c[i] > 1):
+            s[b[i] + lane] = s[b[i] + 64 + lane]
+    g.pairs[3].copy_(torch.as_tensor(s))
+    assert np.array_equal(headers(g), h)
+    assert not np.array_equal(sums(g, st, params, extra)["rho_sum"], before["rho_sum"])
+    same_without_hints(g, st, params, extra)

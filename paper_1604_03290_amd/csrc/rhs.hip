@@ -29,23 +29,27 @@ namespace sph {
 namespace {
 
 // --------------------------------------------------------------- prepass --
-// the slot of every user index: inv[perm[s]] = s
+// the slot of every user index: inv[perm[s]] = s; mass (null unless asked for): the masses
+// m in slot order
 __global__ __launch_bounds__(kBlock) void k_invert(const int32_t *__restrict__ perm, int64_t n,
-                                                   int32_t *__restrict__ inv) {
+                                                   int32_t *__restrict__ inv,
+                                                   const double *__restrict__ m,
+                                                   double *__restrict__ mass) {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < n) inv[perm[s]] = (int32_t)s;
+    if (s >= n) return;
+    const int32_t a = perm[s];
+    inv[a] = (int32_t)s;
+    if (mass) mass[s] = m[a];
 }
 
 // dd3 / nact (null unless requested): the damage model's rates (section 3.2).  With
 // inv (user-order state, its inverse permutation) thread i takes user particle i, so
 // the state arrays are read in order and each thread writes its slot's whole 128-byte
-// record; without it (slot-ordered state) thread i takes slot i.  mass (null unless
-// asked for): the masses in slot order.
+// record; without it (slot-ordered state) thread i takes slot i.
 __global__ __launch_bounds__(kBlock) void k_prepass(GridDev g, StateDev st, int64_t n, Consts k,
                                                     double *__restrict__ rec,
                                                     int32_t *__restrict__ status, double *dd3,
-                                                    int32_t *nact, const int32_t *__restrict__ inv,
-                                                    double *__restrict__ mass) {
+                                                    int32_t *nact, const int32_t *__restrict__ inv) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int64_t s = inv ? (int64_t)inv[i] : i;
@@ -54,7 +58,6 @@ __global__ __launch_bounds__(kBlock) void k_prepass(GridDev g, StateDev st, int6
     const double d = st.d ? st.d[a] : 0.0, rho = st.rho[a], m = st.m[a];
     const double p = write_rec(g, k, s, st.x[a], st.y[a], st.z[a], st.vx[a], st.vy[a], st.vz[a],
                                rho, S, m, rec, status, st.u ? st.u[a] : 0.0, d);
-    if (mass) mass[s] = m;
     if (dd3) {
         const double f = (1.0 - d) * yield_factor(k, S);
         const double ph = p >= 0.0 ? p : (1.0 - d) * p;
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(64 * P) void k_pairs64_list(GridDev g, int64_t n, C
 // from LDS one step ahead.  The mass alone comes from memory by the entry (mass: [n] in slot
 // order), two chunks ahead: the address unit is idle here, and an eighth LDS read a step
 // costs more (V rho in the mass's place is one rounding off; right-hand side of 262,144
-// particles with V rho 160 us, with the mass from memory 166, from the window 171; with the
+// particles with V rho 160 us, with the mass from memory 165, from the window 171; with the
 // extended terms, whose registers do not allow it, 213 with V rho and 223 from the window).
 // The kernel above is bound by its gathers (the texture
 // addresser takes 64 B a clock and CU at best: 112 B a pair), this one by the pairs' FP64
@@ -729,7 +732,7 @@ __global__ __launch_bounds__(64 * kSplit) void k_pairs32_list(GridDev g, int64_t
 
 int invert_launch(const GridDev &g, int64_t n, int32_t *inv, hipStream_t s) {
     if (!g.io) return SPH_OK;
-    k_invert<<<blocks_for(n), kBlock, 0, s>>>(g.io, n, inv);
+    k_invert<<<blocks_for(n), kBlock, 0, s>>>(g.io, n, inv, nullptr, nullptr);
     SPH_LAUNCHED();
     return SPH_OK;
 }
@@ -737,13 +740,14 @@ int invert_launch(const GridDev &g, int64_t n, int32_t *inv, hipStream_t s) {
 int prepass_launch(const GridDev &g, const StateDev &st, int64_t n, const Consts &k, double *rec,
                    int32_t *status, hipStream_t s, const OutDev *od, int32_t *inv, double *mass) {
     if (g.io && inv) {
-        k_invert<<<blocks_for(n), kBlock, 0, s>>>(g.io, n, inv);
+        k_invert<<<blocks_for(n), kBlock, 0, s>>>(g.io, n, inv, st.m, mass);
         SPH_LAUNCHED();
     } else {
+        if (mass) return fail(SPH_ERR_NOT_IMPLEMENTED, "masses are put in slot order with inv only");
         inv = nullptr;
     }
     k_prepass<<<blocks_for(n), kBlock, 0, s>>>(g, st, n, k, rec, status, od ? od->dd3 : nullptr,
-                                               od ? od->n_act : nullptr, inv, mass);
+                                               od ? od->n_act : nullptr, inv);
     SPH_LAUNCHED();
     return SPH_OK;
 }

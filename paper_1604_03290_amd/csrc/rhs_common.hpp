@@ -915,7 +915,7 @@ int invert_launch(const GridDev &g, int64_t n, int32_t *inv, hipStream_t s);
 // od (nullable): outputs whose dd3 / n_act, when set, receive the damage rates
 // inv (nullable): n int32 of scratch; with a user-ordered state the prepass fills it with
 // the inverse permutation and reads the state in user order
-// mass (nullable): [n], the masses in slot order
+// mass (nullable; with a user-ordered state and inv): [n], the masses in slot order
 int prepass_launch(const GridDev &g, const StateDev &st, int64_t n, const Consts &k, double *rec,
                    int32_t *status, hipStream_t s, const OutDev *od = nullptr,
                    int32_t *inv = nullptr, double *mass = nullptr);

@@ -90,7 +90,7 @@ __device__ inline void moment_add(double M[6], double V, double F, double rx, do
 template <bool kCorr>
 __global__ __launch_bounds__(kBlock) void k_adj_L(GridDev g, int64_t n, Consts k,
                                                   const double *__restrict__ rec, AdjRec ad) {
-    const int64_t s = xcd_block(gridDim.x) * kBlock + threadIdx.x;
+    const int64_t s = xcd_cell_block(gridDim.x) * kBlock + threadIdx.x;
     if (s >= n) return;
     const double2 *ra = rec2(rec, s);
     const double2 p0 = ra[0], p1 = ra[1], p2 = ra[2];
@@ -485,7 +485,7 @@ template <bool kCorr, int kEos, bool kAS, bool kXC>
 __global__ __launch_bounds__(kBlock) void k_adj_pairs(GridDev g, int64_t n, Consts k,
                                                       const double *__restrict__ rec, StateDev st,
                                                       AdjRec ad, GradDev out) {
-    const int64_t s = xcd_block(gridDim.x) * kBlock + threadIdx.x;
+    const int64_t s = xcd_cell_block(gridDim.x) * kBlock + threadIdx.x;
     double y0_part = 0.0;
     if (s < n) {
         const AdjOwn o = adj_own(rec, ad, s);

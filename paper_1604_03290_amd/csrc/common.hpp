@@ -198,6 +198,17 @@ __device__ inline int64_t xcd_list_block(int64_t nblocks) {
     return xcd_block(nblocks, nblocks < 4096 ? 8 : kXcdRun);
 }
 
+// And for the adjoint's kernels straight from the cells, whose workgroups take 256 slots, a
+// lane each: runs of 24 from 512 of them on (fewer keep one range per XCD), since runs of 64
+// are few and a dense body's are some XCDs' only.  (us with one range, runs of 64, 24 and 16:
+// adjoint of 150,000 non-uniform particles 3,117, 2,915, 2,440 and 2,255, of 400,000 5,182,
+// 5,757, 4,807 and 4,811, of 600,000 7,649, 7,723, 6,854 and 6,620; of 140,000 on a lattice
+// 1,171, 1,166, 1,181 and 1,207, of 450,000 2,608, 2,606, 2,640 and 2,649; below the line
+// 60,000 in two spheres 604 with one range, 625 with runs of 16.)
+__device__ inline int64_t xcd_cell_block(int64_t nblocks) {
+    return xcd_block(nblocks, nblocks < 512 ? kXcdRun : 24);
+}
+
 // Calls f(t) for every candidate slot t != s of slot s: from the pair list when
 // the grid has one, otherwise by sweeping the cell rows within reach.
 template <class F>

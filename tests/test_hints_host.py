@@ -1,4 +1,5 @@
-"""The pair list's hint kernel on the CPU (tests/wave: a wavefront of 64 fibers).
+"""The pair list's hint kernel on the CPU (tests/wave: a wavefront of 64 fibers), and two
+functions of the pair kernels.
 
 A group's pages go into a table of 512 places; a group that names more than 384 pages gets
 no hints.  The kernel counts the pages once per chunk of 256 entries, each of which can
@@ -135,3 +136,11 @@ def test_places_of_a_window(lib, width):
     max_locals = limits(lib)[2]
     assert [lib.window_place(width, l) for l in range(max_locals + 1)] == [l % width for l in range(max_locals + 1)]
     assert all(0 <= lib.window_place(width, l) < width for l in range(1 << 16))
+
+
+@pytest.mark.parametrize("run", [64, 24, 8, 0, -1])
+def test_every_workgroup_is_placed_once(lib, run):
+    """The order in which workgroups go to the XCDs, at and beside whole rounds of runs."""
+    lib.placed.restype = C.c_int64
+    for n in (1, 7, 8, 9, 63, 64, 65, 191, 192, 193, 511, 512, 513, 1024, 1562, 4095, 4096, 4097):
+        assert sorted(lib.placed(n, i, run) for i in range(n)) == list(range(n))

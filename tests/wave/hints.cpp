@@ -28,3 +28,10 @@ extern "C" int window_place(int width, int local) {
     default: return -1;
     }
 }
+
+// The workgroup that takes the place of workgroup i of n: in runs of `run`, 0: as the kernels
+// over a list have them, -1: as the adjoint's over the cells.
+extern "C" int64_t placed(unsigned n, unsigned i, int run) {
+    wave::w.block = i;
+    return run > 0 ? sph::xcd_block(n, run) : run == 0 ? sph::xcd_list_block(n) : sph::xcd_cell_block(n);
+}

@@ -191,9 +191,12 @@ __device__ inline int64_t xcd_block(int64_t nblocks, int64_t run = kXcdRun) {
 
 // The same for the list kernels, whose workgroups take 64 slots each.  Below 4,096 of them
 // (16 a CU) an XCD has few runs of 64, and a body's dense middle is one XCD's or two: runs
-// of 8 there.  (us with runs of 64, 16 and 8: right-hand side of 50,364 non-uniform
-// particles 146, 128 and 103, of 90,000 223, 172 and 164, adjoint of 95,177 459, 358 and
-// 359; at 4,096 workgroups of a uniform set 64 is the faster by 0.6 %.)
+// of 8 there.  (us with runs of 8, 32 and 64: right-hand side of 60,000 non-uniform particles
+// 116, 121 and 123, of 120,000 182, 211 and 202, of 180,000 253, 265 and 306, of 250,000 344,
+// 341 and 357, their adjoint alike; 250,000 on a lattice 158, 157 and 157, in two spheres
+// 188, 184 and 184.  Beyond the line runs of 8 still gain for non-uniform sets, 300,000 403
+// against 437, 700,000 880 against 946, two million 2,496 against 2,496, and lose for uniform
+// ones, 1,500,000 873 against 869 and 1,130 against 1,115: the uniform kernels keep 64.)
 __device__ inline int64_t xcd_list_block(int64_t nblocks) {
     return xcd_block(nblocks, nblocks < 4096 ? 8 : kXcdRun);
 }

@@ -34,8 +34,8 @@ __device__ inline int wave_max_i32(int v) {
 // at every step, took 150 us on 262,144 particles; four wavefronts on one group with
 // compare-and-swap 110; pages of 64, whose locals follow the steps less closely, made the
 // pair kernels of dense sets slower by a fifth; numbers given by the fill itself, as it
-// meets the candidates, took three times the fill's own time.  This takes 83 us, and 3.8 ms
-// on an 8,388,608-particle non-uniform set, where it moves 13 GB.)
+// meets the candidates, took three times the fill's own time.  This takes 85 us on the
+// 262,144 particles.)
 constexpr int kPageTable = 512;
 constexpr int kMaxPages = 384;       // pages of a group with hints: probes stay short
 constexpr int kBatch = 4;            // chunks whose entries are loaded together

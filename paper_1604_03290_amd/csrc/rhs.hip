@@ -205,13 +205,13 @@ __global__ __launch_bounds__(64 * P) void k_pairs64_list(GridDev g, int64_t n, C
 // costs more (V rho in the mass's place is one rounding off; right-hand side of 262,144
 // particles with V rho 160 us, with the mass from memory 165, from the window 171; with the
 // extended terms, whose registers do not allow it, 213 with V rho and 223 from the window).
-// The kernel above is bound by its gathers (the texture
-// addresser takes 64 B a clock and CU at best: 112 B a pair), this one by the pairs' FP64
-// arithmetic and LDS reads (118 and 73 cycles a step and CU): 262,144 particles with a
-// skin of 0.15 spacings 172 us of gathers, 121 here; with the extended terms 222 and 162;
-// two workgroups a CU are enough, since a step waits for no memory.
-// Without a skin the hints are not built: they cost 83 us on 262,144 particles, more than
-// the 51 us of one evaluation, and such a list holds for one set of positions only.
+// The kernel above is bound by its gathers (the texture addresser takes 64 B a clock and CU
+// at best: 112 B a pair), this one by the pairs' FP64 arithmetic and LDS reads: the whole
+// right-hand side of 262,144 particles with a skin of 0.15 spacings 210 us with the gathers,
+// 165 here; with the extended terms 272 and 223; two workgroups a CU are enough, since a step
+// waits for no memory.
+// Without a skin the hints are not built: they cost 85 us on 262,144 particles, more than
+// the 45 us of one evaluation, and such a list holds for one set of positions only.
 constexpr int kFwdWaves = 4;
 
 template <bool kCorr, bool kExt, int P = kFwdWaves>
@@ -356,9 +356,9 @@ struct LastChunk<true> {
 // the slots that have run out of partners (a lane walking its own slot's cells is idle at
 // three candidates of four, some other lane's partners), and a small set still has a
 // workgroup per 64 slots.  The tests (12 instructions per candidate and 64 slots) and the
-// evaluation each bound it about as much as the search for candidates does.  One slot per
-// lane in workgroups of 256 took 234 us on 4,096 particles and 309 us on 110,592; this
-// takes 40 and 185, and with the extended terms 364 us are now 240.
+// evaluation each bound it about as much as the search for candidates does.  With one
+// slot per lane in workgroups of 256 the whole right-hand side took 241 us for 4,096
+// particles, 310 for 110,592 and, with the extended terms, 366; with this 54, 199 and 239.
 constexpr int kCellWaves = 4;
 
 template <bool kCorr, bool kExt, int P = kCellWaves>

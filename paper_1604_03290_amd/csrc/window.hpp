@@ -2,11 +2,12 @@
 //
 // The 64 slots of a block lie close together, so their lists name the same partners over
 // and over (on a lattice with 57 partners about 460 different slots in 3,500 entries,
-// with 250 partners 980 in 14,200).  The list kernels therefore load every partner of a
-// block once, into the workgroup's LDS, and each lane reads its step's partner from
-// there.  For that sph_build_pairs numbers, where the list has a skin, the block's partners ("locals", in the order
-// of the sweep that found them; every list is in that order) and leaves, in the part of
-// the block's room that its entries do not use,
+// with 250 partners 980 in 14,200).  Over a list with a skin that is not too dense
+// (through_window) the FP64 sums therefore load every partner of a block once, into the
+// workgroup's LDS, and each lane reads its step's partner from there.  For that
+// sph_build_pairs numbers the block's partners ("locals", in the order of the sweep that
+// found them; every list is in that order) and leaves, in the part of the block's room that
+// its entries do not use,
 //   words of a room of b rows of 64
 //     [64 b - 128, 64 b)            header: magic, locals, steps; from word 64 on, for
 //                                   every round of 32 steps the lowest local named from

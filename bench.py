@@ -81,12 +81,12 @@ WORKLOADS = {"two_spheres": 1, "bullet": 2, "nonuniform": 4}
 COUNTERS = {
     "k_adj_pairs_list": {
         "profile": "profiles/hbm_traffic_nonuniform_8388608.md",
-        "fetch_bytes": 18904867306.3, "write_bytes": 3441590822.4, "l2_hit_rate": 0.8253,
-        "sources_sha256": "d50f26073ac481aca594152530ad9ee05b907407d9c00cac8a911c854521240f"},
+        "fetch_bytes": 18866639666.1, "write_bytes": 3446338630.4, "l2_hit_rate": 0.8258,
+        "sources_sha256": "f6497dc0e2968f5cae34ce5c5da86f36397c8f47f732f87beddeb1a0a8d56b67"},
     "k_pairs64_list": {
         "profile": "profiles/hbm_traffic_nonuniform_8388608.md",
-        "fetch_bytes": 15217118768.1, "write_bytes": 3370792296.0, "l2_hit_rate": 0.7515,
-        "sources_sha256": "843c3625ab4ee64232b5d8ebb68b42e50828ae1844cb4493d532214c9b32b5e2"},
+        "fetch_bytes": 15217027509.0, "write_bytes": 3371919976.0, "l2_hit_rate": 0.7520,
+        "sources_sha256": "729d5967c9362ed3ca79af4619818c27e075e2a9805f1fe3c86c0a92333739fa"},
 }
 
 KERNEL_SOURCES = {"k_adj_pairs_list": ("adjoint.hip", "adjoint.hpp", "rhs_common.hpp", "common.hpp"),
